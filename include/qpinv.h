@@ -409,6 +409,8 @@ int qpinv_qgemm_cfg(qpinv_ctx* ctx, int gemm_prec, int cfg, const qpinv_qmat* A,
  * launches is bracketed by HIP events on its stream.  For each kernel used since the previous call
  * (product precision x tile configuration) one row of 5 doubles is written to `out` (host):
  * {gemm_prec, tile configuration, launches, algorithmic flops (32 M N K each), summed event ms}.
+ * The solvers' eight-product form of FP64 and FP32 (16 M N K operations executed) has the numbers behind the
+ * type's tile configurations; qpinv_tile_config_name names them (f64x8_..., f32x8_...).
  * At most max_rows rows; returns the number of rows (>= 0) or an error (EINVAL, EHIP).  The call
  * waits for the recorded events and resets the counters. */
 int qpinv_gemm_stats(qpinv_ctx* ctx, double* out, int max_rows);

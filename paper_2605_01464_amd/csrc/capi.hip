@@ -1,4 +1,5 @@
 // extern "C" boundary of libqpinv.so: argument checks, error codes, no exceptions across the ABI.
+#include <algorithm>
 #include <cstring>
 #include <fstream>
 #include <iterator>
@@ -533,7 +534,9 @@ int qpinv_tune_save(qpinv_ctx* c, const char* path) {
     f.device = tune_device(cx.device);
     for (const auto& e : cx.tuned) {
       const int p = std::get<0>(e.first);
-      f.gemm.emplace_back(p, std::get<1>(e.first), std::get<2>(e.first), std::get<3>(e.first),
+      // the eight-product forms under the type's own number: their configuration names tell them apart
+      const int pt = p == qp::P_F64E ? qp::P_F64 : p == qp::P_F32E ? qp::P_F32 : p;
+      f.gemm.emplace_back(pt, std::get<1>(e.first), std::get<2>(e.first), std::get<3>(e.first),
                           qp::tile_configs((qp::Prec)p).at(e.second).name);
     }
     for (const auto& e : cx.batched_tuned) f.batched.emplace_back(e.first, qp::batched_config_name(e.second));
@@ -559,13 +562,15 @@ int qpinv_tune_load(qpinv_ctx* c, const char* path) {
     // names to indices; entries whose configuration this library does not have are skipped
     int applied = 0;
     for (const auto& g : f.gemm) {
-      const auto& t = qp::tile_configs((qp::Prec)std::get<0>(g));
-      for (int k = 0; k < (int)t.size(); ++k)
-        if (std::get<4>(g) == t[k].name) {
-          cx.tuned[std::make_tuple(std::get<0>(g), std::get<1>(g), std::get<2>(g), std::get<3>(g))] = k;
-          ++applied;
-          break;
-        }
+      const int p = std::get<0>(g);
+      for (int q : {p, p == qp::P_F64 ? (int)qp::P_F64E : p == qp::P_F32 ? (int)qp::P_F32E : p}) {
+        const auto& t = qp::tile_configs((qp::Prec)q);
+        const auto hit = std::find_if(t.begin(), t.end(), [&](const qp::TileConfig& x) { return std::get<4>(g) == x.name; });
+        if (hit == t.end()) continue;
+        cx.tuned[std::make_tuple(q, std::get<1>(g), std::get<2>(g), std::get<3>(g))] = (int)(hit - t.begin());
+        ++applied;
+        break;
+      }
     }
     for (const auto& b : f.batched)
       for (int k = 0; k < qp::batched_num_configs(); ++k)
@@ -586,6 +591,10 @@ int qpinv_num_tile_configs(int gemm_prec) {
 const char* qpinv_tile_config_name(int gemm_prec, int cfg) {
   if (gemm_prec < QPINV_GEMM_F64 || gemm_prec > QPINV_GEMM_BF16X3) return "";
   const auto& t = qp::tile_configs((qp::Prec)gemm_prec);
+  if (cfg >= (int)t.size() && gemm_prec <= QPINV_GEMM_F32) {  // as the product statistics number the eight-product form
+    const auto& e = qp::tile_configs(gemm_prec == QPINV_GEMM_F64 ? qp::P_F64E : qp::P_F32E);
+    return cfg - (int)t.size() < (int)e.size() ? e[cfg - t.size()].name : "";
+  }
   if (cfg < 0 || cfg >= (int)t.size()) return "";
   return t[cfg].name;
 }

@@ -227,6 +227,8 @@ static const std::vector<F64Entry>& f64_table() {
 
 const std::vector<TileConfig>& bf16_configs();    // qgemm_bf16.hip
 const std::vector<TileConfig>& bf16x3_configs();  // qgemm_bf16.hip
+const std::vector<TileConfig>& eight_configs(Prec p);  // qgemm8.hip
+int eight_default(Prec p, int64_t M, int64_t N, int64_t K);
 
 const std::vector<TileConfig>& tile_configs(Prec p) {
   static std::vector<TileConfig> f32, f64;
@@ -236,6 +238,7 @@ const std::vector<TileConfig>& tile_configs(Prec p) {
   }
   if (p == P_BF16) return bf16_configs();
   if (p == P_BF16X3) return bf16x3_configs();
+  if (p == P_F64E || p == P_F32E) return eight_configs(p);
   return p == P_F64 ? f64 : f32;
 }
 
@@ -255,7 +258,7 @@ int64_t qgemm_blocks(Prec p, int cfg, int64_t M, int64_t N) {
 // of 64 x 64: the staged form with its operand tiles loaded straight into LDS; split BF16: 128 x 128 tiles
 // from 256 of them (one workgroup of 16 waves per CU), 64 x 64 below.
 int default_config(Prec p, int64_t M, int64_t N, int64_t K) {
-  (void)K;
+  if (p == P_F64E || p == P_F32E) return eight_default(p, M, N, K);
   const int64_t b64 = ((M + 63) / 64) * ((N + 63) / 64);
   if (p == P_F64) return b64 >= 1024 ? 6 : 1;
   if (p == P_BF16) return b64 >= 1024 ? 11 : b64 >= 256 ? 0 : 1;
@@ -302,6 +305,8 @@ int64_t bf16_launch(const GemmParams<float>& P, int cfg, hipStream_t s, GemmScra
 int64_t bf16_blocks(int cfg, int64_t M, int64_t N);
 int64_t bf16x3_launch(const GemmParams<float>& P, int cfg, hipStream_t s, GemmScratch& scratch);
 int64_t bf16x3_blocks(int cfg, int64_t M, int64_t N);
+int64_t f64x8_launch(const GemmParams<double>& P, int cfg, hipStream_t s);  // qgemm8.hip
+int64_t f32x8_launch(const GemmParams<float>& P, int cfg, hipStream_t s);
 
 void qgemm(Prec p, const QView& A, const QView& B, int64_t M, int64_t N, int64_t K, const Epilogue& epi,
            double* red, GemmScratch& scratch, hipStream_t stream, int cfg) {
@@ -318,7 +323,12 @@ void qgemm(Prec p, const QView& A, const QView& B, int64_t M, int64_t N, int64_t
   if (epi.reduce && nb > scratch.capacity / 2) throw Error(-1, "qgemm: reduction scratch too small");
   double* partial = epi.reduce ? scratch.partial : nullptr;
   int64_t launched = 0;
-  if (p == P_F64) {
+  if ((p == P_F64E || p == P_F32E) && !eight_fits(p, A, B, M, K)) throw Error(-1, "qgemm: operands of the eight-product form");
+  if (p == P_F64E) {
+    launched = f64x8_launch(make_params<double>(A, B, M, N, K, epi, partial), cfg, stream);
+  } else if (p == P_F32E) {
+    launched = f32x8_launch(make_params<float>(A, B, M, N, K, epi, partial), cfg, stream);
+  } else if (p == P_F64) {
     launched = f64_table()[cfg].fn(make_params<double>(A, B, M, N, K, epi, partial), stream);
   } else if (p == P_F32) {
     launched = f32_table()[cfg].fn(make_params<float>(A, B, M, N, K, epi, partial), stream);

@@ -19,7 +19,8 @@
 namespace qp {
 
 // P_BF16X3: FP32 storage, each product as three BF16 products of split operands (hi.hi + hi.lo + lo.hi)
-enum Prec : int { P_F64 = 0, P_F32 = 1, P_BF16 = 2, P_BF16X3 = 3 };
+// P_F64E, P_F32E: FP64 / FP32 with eight real products per quaternion product (qgemm8_kern.hpp); inside the solvers only
+enum Prec : int { P_F64 = 0, P_F32 = 1, P_BF16 = 2, P_BF16X3 = 3, P_F64E = 4, P_F32E = 5 };
 
 struct Epilogue {
   int nout = 1;
@@ -77,6 +78,8 @@ void qgemm(Prec p, const QView& A, const QView& B, int64_t M, int64_t N, int64_t
 
 // Number of workgroups a configuration launches for an M x N output (sizes scratch).
 int64_t qgemm_blocks(Prec p, int cfg, int64_t M, int64_t N);
+// whether the operands of an M x N x K product suit the eight-product form p (P_F64E, P_F32E)
+bool eight_fits(Prec p, const QView& A, const QView& B, int64_t M, int64_t K);
 // whether a P_BF16X3 product of this shape fits the split copies' 32-bit buffer offsets
 bool bf16x3_fits(int64_t M, int64_t N, int64_t K);
 

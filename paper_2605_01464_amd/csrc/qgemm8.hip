@@ -1,0 +1,138 @@
+// Launches of the eight-product form (qgemm8_kern.hpp): configuration tables and the choice between them.
+#include <algorithm>
+#include <vector>
+
+#include "qgemm8_kern.hpp"
+
+namespace qp {
+
+template <class MM, int BM, int BN, int WM, int WN, int FLUSH, int MINW>
+__global__ void __launch_bounds__(64 * WM * WN, MINW) qgemm8_kernel(GemmParams<typename MM::T> P) {
+  using C = Gemm8Cfg<MM, BM, BN, WM, WN>;
+  __shared__ __attribute__((aligned(16))) typename MM::T smem[2 * C::STAGE];
+  __shared__ double red_lds[C::NW][2];
+  double s_d = 0.0, s_x = 0.0;
+  int tm, tn;
+  tile_of_block(blockIdx.x, P.tiles_m * P.tiles_n, P.tiles_m, P.tiles_n, tm, tn);
+  gemm8_tile<MM, BM, BN, WM, WN, FLUSH>(P, tm, tn, smem, s_d, s_x);
+  store_partials<C::NW>(P.partial, s_d, s_x, red_lds, threadIdx.x & 63, threadIdx.x >> 6, threadIdx.x);
+}
+
+template <class MM, int TM, int TN, int NWV, int MINW>
+__global__ void __launch_bounds__(64 * NWV, MINW) qgemm8_regs_kernel(GemmParams<typename MM::T> P) {
+  __shared__ __attribute__((aligned(16))) typename MM::T smem[NWV * 4 * 256 * TM * TN];
+  __shared__ double red_lds[NWV][2];
+  double s_d = 0.0, s_x = 0.0;
+  int tm, tn;
+  tile_of_block(blockIdx.x, P.tiles_m * P.tiles_n, P.tiles_m, P.tiles_n, tm, tn);
+  gemm8_regs_tile<MM, TM, TN, NWV>(P, tm, tn, smem, s_d, s_x);
+  store_partials<NWV>(P.partial, s_d, s_x, red_lds, threadIdx.x & 63, threadIdx.x >> 6, threadIdx.x);
+}
+
+template <class MM, int BM, int BN, int WM, int WN, int FLUSH, int MINW>
+static int64_t launch8(const GemmParams<typename MM::T>& P0, hipStream_t s) {
+  using C = Gemm8Cfg<MM, BM, BN, WM, WN>;
+  GemmParams<typename MM::T> P = P0;
+  P.tiles_m = (P.M + BM - 1) / BM;
+  P.tiles_n = (P.N + BN - 1) / BN;
+  const int64_t nt = (int64_t)P.tiles_m * P.tiles_n;
+  if (nt == 0) return 0;
+  hipLaunchKernelGGL((qgemm8_kernel<MM, BM, BN, WM, WN, FLUSH, MINW>), dim3((unsigned)nt), dim3(C::NT), 0, s, P);
+  QP_HIP(hipGetLastError());
+  return nt;
+}
+
+template <class MM, int TM, int TN, int NWV, int MINW>
+static int64_t launch8_regs(const GemmParams<typename MM::T>& P0, hipStream_t s) {
+  GemmParams<typename MM::T> P = P0;
+  P.tiles_m = (P.M + 16 * TM - 1) / (16 * TM);
+  P.tiles_n = (P.N + 16 * TN - 1) / (16 * TN);
+  const int64_t nt = (int64_t)P.tiles_m * P.tiles_n;
+  if (nt == 0) return 0;
+  hipLaunchKernelGGL((qgemm8_regs_kernel<MM, TM, TN, NWV, MINW>), dim3((unsigned)nt), dim3(64 * NWV), 0, s, P);
+  QP_HIP(hipGetLastError());
+  return nt;
+}
+
+template <class T>
+struct Entry8 {
+  TileConfig cfg;
+  int64_t (*fn)(const GemmParams<T>&, hipStream_t);
+};
+
+// Three tiles each: 64 x 64 (8 waves, one workgroup per compute unit) and 32 x 32 (4 waves, two per unit) through LDS, and
+// 16 x 16 in registers (4 waves, each every fourth block of k; two workgroups per unit in FP64, three in FP32).
+static const std::vector<Entry8<double>>& f64_table8() {
+  static const std::vector<Entry8<double>> t = {
+      {{0, 64, 64, 8, 512, "f64x8_64x64_w2x4"}, launch8<MM16D, 64, 64, 2, 4, 0, 2>},
+      {{1, 32, 32, 8, 256, "f64x8_32x32_w2x2"}, launch8<MM16D, 32, 32, 2, 2, 0, 2>},
+      {{2, 16, 16, 8, 256, "f64x8_16x16_regs4"}, launch8_regs<MM16D, 1, 1, 4, 2>},
+  };
+  return t;
+}
+
+// FP32 sums over k are flushed every 128 k, as in the direct form.  The register form does not flush: each wave sums a
+// quarter of k, which kRegsMaxK keeps at 512, the 128 dependent MFMAs that the direct form's 128 k take.
+static const std::vector<Entry8<float>>& f32_table8() {
+  static const std::vector<Entry8<float>> t = {
+      {{0, 64, 64, 16, 1024, "f32x8_64x64_w4x4"}, launch8<MM16F, 64, 64, 4, 4, 128, 4>},
+      {{1, 32, 32, 16, 256, "f32x8_32x32_w2x2"}, launch8<MM16F, 32, 32, 2, 2, 128, 2>},
+      {{2, 16, 16, 16, 256, "f32x8_16x16_regs4"}, launch8_regs<MM16F, 1, 1, 4, 3>},
+  };
+  return t;
+}
+constexpr int64_t kRegsMaxK = 2048;
+
+const std::vector<TileConfig>& eight_configs(Prec p) {
+  auto list = [](const auto& table) {
+    std::vector<TileConfig> v;
+    for (auto& e : table) v.push_back(e.cfg);
+    return v;
+  };
+  static const std::vector<TileConfig> c64 = list(f64_table8()), c32 = list(f32_table8());
+  return p == P_F64E ? c64 : c32;
+}
+
+// The tile that takes the least time by a model of rounds: with `cap` workgroups resident on the chip, every full round costs
+// full x K microseconds and the last, partial one `part` x K if it leaves at most one workgroup per unit.  Measured, FP64 (us):
+//   K = 300, 300 x 300:    64 x 64 91    32 x 32 36    16 x 16 21     (direct form 55)
+//   K = 1000, 500 x 500:   64 x 64 268   32 x 32 107   16 x 16 101    (170)
+//   K = 700, 700 x 700:    64 x 64 197   32 x 32 132   16 x 16 156    (204)
+//   K = 1000, 1000 x 1000: 64 x 64 304   32 x 32 364   16 x 16 415    (564)
+//   K = 4096, 4096 x 4096: 64 x 64 17089 32 x 32 20071                (30600; 64.3 TFLOP/s of MFMA work)
+// and FP32: 300^3 49 / 23 / 14 (41), 700^3 107 / 74 / 88 (138), 1000^3 163 / 200 / 251 (326), 4096^3 8863 / 10760 (15931).
+int eight_default(Prec p, int64_t M, int64_t N, int64_t K) {
+  struct Cost {
+    int64_t tile, cap;
+    double full, part, fixed;
+  };
+  static constexpr Cost k64[3] = {{64, 256, 0.27, 0.27, 12}, {32, 512, 0.175, 0.1, 6}, {16, 512, 0.053, 0.025, 3}};
+  static constexpr Cost k32[3] = {{64, 256, 0.14, 0.14, 10}, {32, 512, 0.1, 0.062, 5}, {16, 768, 0.049, 0.017, 3}};
+  int best = 0;
+  double best_t = 0.0;
+  for (int i = 0; i < 3; ++i) {
+    const Cost& c = (p == P_F64E ? k64 : k32)[i];
+    if (p == P_F32E && c.tile == 16 && K > kRegsMaxK) continue;
+    const int64_t tiles = ((M + c.tile - 1) / c.tile) * ((N + c.tile - 1) / c.tile), rest = tiles % c.cap;
+    const double t = (double)K * ((double)(tiles / c.cap) * c.full + (rest == 0 ? 0.0 : rest <= 256 ? c.part : c.full)) + c.fixed;
+    if (i == 0 || t < best_t) {
+      best = i;
+      best_t = t;
+    }
+  }
+  return best;
+}
+
+// Rows on 16-byte boundaries, lane offsets within a plane that fit 32 bits, and a K from which on the form's rounding error is
+// the smaller one (FP32, sequential sums, iid planes: 1.12e-7 against the direct form's 1.08e-7 at K = 8, 1.69e-7 against
+// 2.09e-7 at K = 32).
+bool eight_fits(Prec p, const QView& A, const QView& B, int64_t M, int64_t K) {
+  const int64_t es = p == P_F64E ? 8 : 4, va = 16 / es;
+  auto al = [&](const QView& v) { return (reinterpret_cast<uintptr_t>(v.p) & 15) == 0 && v.ld % va == 0 && v.ps % va == 0; };
+  return al(A) && al(B) && M * A.ld * es < (int64_t(1) << 31) && 16 * B.ld * es < (int64_t(1) << 31) && K >= 16;
+}
+
+int64_t f64x8_launch(const GemmParams<double>& P, int cfg, hipStream_t s) { return f64_table8()[cfg].fn(P, s); }
+int64_t f32x8_launch(const GemmParams<float>& P, int cfg, hipStream_t s) { return f32_table8()[cfg].fn(P, s); }
+
+}  // namespace qp

@@ -1451,10 +1451,7 @@ int small_solve_t(Ctx& c, int method, int order, const Mat& A0, int scaling, dou
 
 }  // namespace
 
-bool small_eligible(const Ctx& c, int method, int order, int scaling, int stop, int precision, int64_t m, int64_t n) {
-  if (!c.opt.small_path || c.opt.gemm_timing || c.opt.penrose_finish) return false;
-  for (int k = 0; k < 3; ++k)
-    if (c.opt.force_cfg[k] >= 0) return false;
+bool small_takes(int method, int order, int scaling, int stop, int precision, int64_t m, int64_t n) {
   if (precision != QPINV_PREC_F64 && precision != QPINV_PREC_F32) return false;
   if (method == QPINV_QRAPID) {
     if (qrapid_phases(order, true) > SM_MAXPH || qrapid_phases(order, false) > SM_MAXPH) return false;
@@ -1464,6 +1461,13 @@ bool small_eligible(const Ctx& c, int method, int order, int scaling, int stop, 
   if (stop != STOP_DX_ABS && stop != STOP_DX_REL && stop != STOP_E1_REL) return false;
   if (scaling != QPINV_ALPHA_POWER && scaling != QPINV_ALPHA_FROB && scaling != QPINV_ALPHA_GIVEN) return false;
   return m >= 1 && n >= 1 && m <= SM_MAXD && n <= SM_MAXD;
+}
+
+bool small_eligible(const Ctx& c, int method, int order, int scaling, int stop, int precision, int64_t m, int64_t n) {
+  if (!c.opt.small_path || c.opt.gemm_timing || c.opt.penrose_finish) return false;
+  for (int k = 0; k < 3; ++k)
+    if (c.opt.force_cfg[k] >= 0) return false;
+  return small_takes(method, order, scaling, stop, precision, m, n);
 }
 
 int small_solve(Ctx& c, int method, int order, const Mat& A0, int scaling, double am, double tol, int max_iter,

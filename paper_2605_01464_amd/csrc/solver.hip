@@ -39,7 +39,7 @@ const double kE2 = -0.25 * kS93;
 const double kC1 = 3.0 / 8.0;
 const double kC2 = 321.0 / 1984.0;
 
-inline int store_of(Prec p) { return p == P_F64 ? QPINV_F64 : QPINV_F32; }
+inline int store_of(Prec p) { return p == P_F64 || p == P_F64E ? QPINV_F64 : QPINV_F32; }
 inline size_t esize(int dtype) { return dtype == QPINV_F64 ? 8 : 4; }
 inline int64_t round8(int64_t x) { return (x + 7) / 8 * 8; }
 
@@ -135,7 +135,7 @@ Ctx::~Ctx() {
 }
 
 int Ctx::config_for(Prec p, int64_t M, int64_t N, int64_t K, hipStream_t s) {
-  if (opt.force_cfg[(int)p] >= 0) return opt.force_cfg[(int)p];
+  if (p <= P_BF16X3 && opt.force_cfg[(int)p] >= 0) return opt.force_cfg[(int)p];
   auto key = std::make_tuple((int)p, M, N, K);
   auto it = tuned.find(key);
   if (it != tuned.end()) return it->second;
@@ -183,6 +183,12 @@ void gemm(Ctx& c, Prec p, const Mat& A, const Mat& B, const Epilogue& e, hipStre
   if (A.cols != B.rows) throw Error(QPINV_EINVAL, "gemm: inner dimensions differ");
   const int64_t M = A.rows, N = B.cols, K = A.cols;
   if (p == P_F32 && c.split_f32 && bf16x3_fits(M, N, K)) p = P_BF16X3;
+  // a tile configuration of the direct form that the caller asks for (gemm_cfg_*) is taken as it is
+  if (c.eight && (p == P_F64 || p == P_F32) && c.opt.force_cfg[(int)p] < 0) {
+    const Prec p8 = p == P_F64 ? P_F64E : P_F32E;
+    if (eight_fits(p8, A.v, B.v, M, K)) p = p8;
+  }
+  const bool eight = p == P_F64E || p == P_F32E;
   const int cfg = c.config_for(p, M, N, K, s);
   const double f = 32.0 * (double)M * (double)N * (double)K;
   c.flops += f;
@@ -200,7 +206,9 @@ void gemm(Ctx& c, Prec p, const Mat& A, const Mat& B, const Epilogue& e, hipStre
   }
   auto& ev = c.events[c.events_used];
   c.event_flops[c.events_used] = f;
-  c.event_key[c.events_used] = (int)p * 64 + cfg;
+  // the eight-product configurations are numbered behind the direct ones of their type
+  c.event_key[c.events_used] = eight ? ((int)p - P_F64E) * 64 + (int)tile_configs((Prec)((int)p - P_F64E)).size() + cfg
+                                     : (int)p * 64 + cfg;
   ++c.events_used;
   QP_HIP(hipEventRecord(ev.first, s));
   qgemm(p, A.v, B.v, M, N, K, e, red, c.scratch, s, cfg);
@@ -895,12 +903,15 @@ int solve(Ctx& c, int method, int order, const qpinv_qmat* Aq, int scaling, doub
     ~SplitScope() { c.split_f32 = false; }
   } split_scope(c, precision == QPINV_PREC_MIXED && c.opt.mixed_split != 0 && !c.no_alloc);
 
-  // A in each storage type on demand
+  // A in each storage type on demand; also a copy of a caller's matrix whose rows are not on 16-byte boundaries, which
+  // every product of A would otherwise load element by element
   Mat Acache[2];
   bool have[2] = {false, false};
+  const int64_t va0 = 16 / (int64_t)esize(A0.dtype);
+  const bool aligned0 = (reinterpret_cast<uintptr_t>(A0.v.p) & 15) == 0 && A0.v.ld % va0 == 0 && A0.v.ps % va0 == 0;
   auto A_of = [&](int dt) -> Mat {
     const int k = dt == QPINV_F64 ? 1 : 0;
-    if (A0.dtype == dt) return A0;
+    if (A0.dtype == dt && aligned0) return A0;
     if (!have[k]) {
       Acache[k] = ws_mat(c, "A", m, n, dt);
       convert_mat(A0, Acache[k], s);
@@ -920,6 +931,18 @@ int solve(Ctx& c, int method, int order, const qpinv_qmat* Aq, int scaling, doub
     QP_HIP(hipStreamSynchronize(s));
     return finish(QPINV_OK);
   }
+
+  // Products with eight real products per quaternion product: A is finite, and with its norm this far inside the range (and
+  // the iterates' with it, up to a condition number of 1e8 and more) no sum of two elements or of four products of them
+  // leaves it.  A solve that the one-launch path would take, but for its scaling or an option, keeps that path's direct
+  // form, so that all of them stop at the same update where the tolerance is the precision's floor.
+  struct EightScope {
+    Ctx& c;
+    EightScope(Ctx& cx, bool on) : c(cx) { c.eight = on; }
+    ~EightScope() { c.eight = false; }
+  } eight_scope(c, !small_takes(method, order, QPINV_ALPHA_POWER, stop, precision, m, n) &&
+                       normA > (precision == QPINV_PREC_F64 ? 1e-100 : 1e-12) &&
+                       normA < (precision == QPINV_PREC_F64 ? 1e100 : 1e12));
 
   // precision phases
   std::vector<Prec> phases;

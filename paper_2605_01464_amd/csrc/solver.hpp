@@ -71,6 +71,8 @@ struct Ctx {
   BatchedState* batched = nullptr;
   std::map<std::vector<int64_t>, int> batched_tuned;  // batch signature -> tile configuration
   bool no_alloc = false;  // allocation-free call in progress: no autotuning, no product timing, no growth
+  bool eight = false;  // a solve in progress whose operands are known to be finite and far from the type's limits: its FP64 and
+                       // FP32 products take the eight-product form
   bool split_f32 = false;  // a ladder solve in progress computes its FP32-storage products as P_BF16X3
   void* small_state = nullptr;  // the small solve's record whose barrier words hold a known count and a clear flag
   unsigned int small_bar_base = 0;  // the arrival count those barrier words hold
@@ -117,7 +119,9 @@ int solve(Ctx& c, int method, int order, const qpinv_qmat* A, int scaling, doubl
 int solve_noalloc(Ctx& c, int method, int order, const qpinv_qmat* A, int scaling, double alpha_or_mu, double tol,
                   int max_iter, int stop, int precision, qpinv_qmat* X, qpinv_info* info, hipStream_t s);
 
-// One-launch solve of a small matrix (small.hip): eligibility and the solve (returns a status code).
+// One-launch solve of a small matrix (small.hip): the solves it takes, whether it takes one under the context's options, and
+// the solve (returns a status code).
+bool small_takes(int method, int order, int scaling, int stop, int precision, int64_t m, int64_t n);
 bool small_eligible(const Ctx& c, int method, int order, int scaling, int stop, int precision, int64_t m, int64_t n);
 int small_solve(Ctx& c, int method, int order, const Mat& A0, int scaling, double am, double tol, int max_iter,
                 int stop, int precision, const Mat& Xout, qpinv_info& inf, hipStream_t s);
