@@ -591,6 +591,7 @@ int qpinv_num_tile_configs(int gemm_prec) {
 const char* qpinv_tile_config_name(int gemm_prec, int cfg) {
   if (gemm_prec < QPINV_GEMM_F64 || gemm_prec > QPINV_GEMM_BF16X3) return "";
   const auto& t = qp::tile_configs((qp::Prec)gemm_prec);
+  if (cfg == qp::kNarrowConfig && gemm_prec <= QPINV_GEMM_F32) return gemm_prec == QPINV_GEMM_F64 ? "f64_16x16_narrow" : "f32_16x16_narrow";
   if (cfg >= (int)t.size() && gemm_prec <= QPINV_GEMM_F32) {  // as the product statistics number the eight-product form
     const auto& e = qp::tile_configs(gemm_prec == QPINV_GEMM_F64 ? qp::P_F64E : qp::P_F32E);
     return cfg - (int)t.size() < (int)e.size() ? e[cfg - t.size()].name : "";

@@ -31,15 +31,90 @@ __global__ void __launch_bounds__(256) dots_kernel(const double* __restrict__ V,
   if (threadIdx.x == 0) out[i] = red[0];
 }
 
-// W[e] += sign * sum_i h[i] V_i[e]   (i < nvec, in index order)
+// W[e] += sign * sum_i h[i] V_i[e]   (i < nvec, in index order).
+//
+// The sum of an element is one chain of nvec multiply-adds, whose order fixes the result: its length (1000 steps of a Krylov
+// run: 4 us) is the floor, and with one thread per element fetching its own operands every step waited for memory (118 us on
+// average at L = 2856 and 1088 steps).  Here a workgroup has 16 elements: its 256 threads fetch CH vectors' 128-byte
+// pieces at a time, a chunk ahead, into LDS, and 16 lanes run the chains from there (average 118 -> 10 us).
+constexpr int AX_E = 16, AX_CH = 128, AX_U = AX_CH * AX_E / 256;
 __global__ void __launch_bounds__(256) multi_axpy_kernel(const double* __restrict__ V, int64_t L,
                                                          const double* __restrict__ h, int nvec, double sign,
                                                          double* __restrict__ W) {
-  for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < L; e += (int64_t)gridDim.x * 256) {
-    double acc = 0.0;
-    for (int i = 0; i < nvec; ++i) acc += h[i] * V[(int64_t)i * L + e];
-    W[e] += sign * acc;
+  __shared__ double vs[2][AX_CH * AX_E], hs[2][AX_CH];
+  const int tid = threadIdx.x;
+  const int64_t e0 = (int64_t)blockIdx.x * AX_E;
+  const int64_t e = min(e0 + (tid % AX_E), L - 1);
+  double r[AX_U], rh = 0.0;
+  auto load = [&](int i0) {
+#pragma unroll
+    for (int u = 0; u < AX_U; ++u) r[u] = V[(int64_t)min(i0 + tid / AX_E + u * (256 / AX_E), nvec - 1) * L + e];
+    if (tid < AX_CH) rh = h[min(i0 + tid, nvec - 1)];
+  };
+  auto store = [&](int b) {
+#pragma unroll
+    for (int u = 0; u < AX_U; ++u) vs[b][tid + u * 256] = r[u];
+    if (tid < AX_CH) hs[b][tid] = rh;
+  };
+  double acc = 0.0;
+  if (nvec > 0) {
+    load(0);
+    store(0);
   }
+  __syncthreads();
+  for (int i0 = 0, b = 0; i0 < nvec; i0 += AX_CH, b ^= 1) {
+    const bool more = i0 + AX_CH < nvec;
+    if (more) load(i0 + AX_CH);
+    if (tid < AX_E) {
+      const int n = min(AX_CH, nvec - i0);
+      const double* v = vs[b] + tid;
+      int i = 0;
+      for (; i + 16 <= n; i += 16) {
+        double x[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) x[u] = v[(i + u) * AX_E];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) acc = fma(hs[b][i + u], x[u], acc);
+      }
+      for (; i < n; ++i) acc = fma(hs[b][i], v[i * AX_E], acc);
+    }
+    if (more) store(b ^ 1);  // last read two chunks ago, behind a barrier
+    __syncthreads();
+  }
+  if (tid < AX_E && e0 + tid < L) W[e0 + tid] = fma(sign, acc, W[e0 + tid]);
+}
+
+// hn[0] = ||W||_F^2 in dots_kernel's order, Y = W / ||W||_F, and the step's 2 nvec projections and hn to `host` (pinned).
+// Every workgroup forms the norm for itself (the vector is at most kFusedNorm doubles long).
+constexpr int64_t kFusedNorm = 16384;
+__global__ void __launch_bounds__(256) norm_scale_kernel(const double* __restrict__ W, int64_t L, const double* __restrict__ h,
+                                                         int nh, double* __restrict__ host, double* __restrict__ Y) {
+  __shared__ double red[256];
+  double acc = 0.0;
+  for (int64_t e = threadIdx.x; e < L; e += 256) acc += W[e] * W[e];
+  red[threadIdx.x] = acc;
+  __syncthreads();
+  for (int off = 128; off > 0; off >>= 1) {
+    if ((int)threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
+    __syncthreads();
+  }
+  const double n2 = red[0];
+  if (blockIdx.x == 0) {
+    for (int i = threadIdx.x; i < nh; i += 256) host[i] = h[i];
+    if (threadIdx.x == 0) host[nh] = n2;
+  }
+  const double a = 1.0 / sqrt(n2);
+  for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < L; e += (int64_t)gridDim.x * 256) Y[e] = a * W[e];
+}
+
+// The same from a norm formed by dots_kernel (longer vectors).
+__global__ void __launch_bounds__(256) scale_by_norm_kernel(const double* __restrict__ W, int64_t L, const double* __restrict__ h,
+                                                            int nh, double* __restrict__ host, double* __restrict__ Y) {
+  const double n2 = h[nh];
+  if (blockIdx.x == 0)
+    for (int i = threadIdx.x; i <= nh; i += 256) host[i] = h[i];
+  const double a = 1.0 / sqrt(n2);
+  for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < L; e += (int64_t)gridDim.x * 256) Y[e] = a * W[e];
 }
 
 // Y = a X
@@ -48,7 +123,29 @@ __global__ void __launch_bounds__(256) scale_kernel(const double* __restrict__ X
   for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < L; e += (int64_t)gridDim.x * 256) Y[e] = a * X[e];
 }
 
+unsigned axpy_blocks(int64_t L) { return (unsigned)((L + AX_E - 1) / AX_E); }
 unsigned blocks_for(int64_t L) { return (unsigned)std::min<int64_t>((L + 255) / 256, 2048); }
+
+// The context's pinned columns, grown on demand, and events.
+double* krylov_columns(Ctx& c, size_t doubles, int events) {
+  if (c.krylov_cap < doubles) {
+    if (c.krylov_buf) (void)hipHostFree(c.krylov_buf);
+    c.krylov_buf = nullptr;
+    c.krylov_cap = 0;
+    if (hipHostMalloc(&c.krylov_buf, sizeof(double) * doubles, hipHostMallocDefault) != hipSuccess) {
+      (void)hipGetLastError();
+      c.krylov_buf = nullptr;
+      throw Error(QPINV_ENOMEM, "krylov: pinned allocation of " + std::to_string(sizeof(double) * doubles) + " bytes failed");
+    }
+    c.krylov_cap = doubles;
+  }
+  while ((int)c.krylov_events.size() < events) {
+    hipEvent_t e;
+    QP_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    c.krylov_events.push_back(e);
+  }
+  return c.krylov_buf;
+}
 
 // a dense n x m view of slot j of the basis array
 Mat slot(double* base, int64_t j, int64_t n, int64_t m) {
@@ -122,22 +219,15 @@ KrylovResult gl_krylov(Ctx& c, int method, const Mat& A, const Mat& B, const Mat
   int k = 0;
   // coefficients y of X_k = X_0 + sum_i y_i V_i after k steps
   auto coefficients = [&](int kk) {
-    std::vector<double> y(kk, 0.0);
-    if (method == 1) {  // GMRES: upper-triangular R y = g (the rotated Hessenberg)
-      for (int i = kk - 1; i >= 0; --i) {
-        double t = g[i];
-        for (int l = i + 1; l < kk; ++l) t -= H[l][i] * y[l];
-        y[i] = t / H[i][i];
-      }
-    } else {  // FOM: H_k y = beta e_1.  The first k - 1 rotations bring the square Hessenberg to R with
-      // its last diagonal entry taken before the last rotation (c rho), and beta e_1 to g with its last
-      // entry taken before the last rotation (g / c).
-      const double c_last = cs[kk - 1];
-      for (int i = kk - 1; i >= 0; --i) {
-        double t = (i == kk - 1) ? g[i] / c_last : g[i];
-        for (int l = i + 1; l < kk; ++l) t -= H[l][i] * y[l];
-        y[i] = t / ((i == kk - 1) ? c_last * H[i][i] : H[i][i]);
-      }
+    // back substitution column by column (H[l] is contiguous)
+    std::vector<double> y(g.begin(), g.begin() + kk);
+    // GMRES: upper-triangular R y = g (the rotated Hessenberg).  FOM: H_k y = beta e_1; the first k - 1 rotations bring the
+    // square Hessenberg to R with its last diagonal entry taken before the last rotation (c rho), and beta e_1 to g with its
+    // last entry taken before the last rotation (g / c).
+    const double c_last = method == 1 ? 1.0 : cs[kk - 1];
+    for (int l = kk - 1; l >= 0; --l) {
+      y[l] = l == kk - 1 ? (y[l] / c_last) / (c_last * H[l][l]) : y[l] / H[l][l];
+      for (int i = 0; i < l; ++i) y[i] -= H[l][i] * y[l];
     }
     return y;
   };
@@ -147,7 +237,7 @@ KrylovResult gl_krylov(Ctx& c, int method, const Mat& A, const Mat& B, const Mat
     QP_HIP(hipMemcpyAsync(dh, y.data(), sizeof(double) * kk, hipMemcpyHostToDevice, s));
     if (Xdst.v.p != X.v.p)
       QP_HIP(hipMemcpyAsync(Xdst.v.p, X.v.p, sizeof(double) * (size_t)L, hipMemcpyDeviceToDevice, s));
-    hipLaunchKernelGGL(multi_axpy_kernel, dim3(blocks_for(L)), dim3(256), 0, s, V, L, dh, kk, 1.0,
+    hipLaunchKernelGGL(multi_axpy_kernel, dim3(axpy_blocks(L)), dim3(256), 0, s, V, L, dh, kk, 1.0,
                        static_cast<double*>(Xdst.v.p));
     QP_HIP(hipGetLastError());
     QP_HIP(hipStreamSynchronize(s));  // y (host) is read by the copy
@@ -157,29 +247,47 @@ KrylovResult gl_krylov(Ctx& c, int method, const Mat& A, const Mat& B, const Mat
     product(c, A, Xs, AV, s, &B, -1.0, 1.0);
     return std::sqrt(dot_self(static_cast<double*>(AV.v.p))) / r0;
   };
-  res.status = QPINV_ENOTCONVERGED;
-  for (int j = 0; j < max_iter; ++j) {
+  // Step j on the stream: W = A V_j (or M A V_j), classical Gram-Schmidt twice (h = V^T W, W -= V h), V_{j+1} = W / ||W||.
+  // Nothing in it waits for the host, which reads the new Hessenberg column from pinned memory kAhead steps behind: the
+  // rotations and the stopping test of one step run while the next ones do (at the end up to kAhead steps are
+  // dropped; they touch only W, AV and basis slots that X does not use).
+  constexpr int kAhead = 3, kRing = kAhead + 1;
+  const int64_t ring = 2 * (int64_t)max_iter + 1;
+  double* const columns = krylov_columns(c, (size_t)(ring * kRing), kRing);
+  auto enqueue = [&](int j) {
     const Mat Vj = slot(V, j, n, m);
-    // W = A V_j, or M (A V_j)
     if (M) {
       product(c, A, Vj, AV, s);
       product(c, *M, AV, W, s);
     } else {
       product(c, A, Vj, W, s);
     }
-    // classical Gram-Schmidt, twice: h = V^T W, W -= V h (on device; h to the host once)
-    // (both passes and the norm of the result queue back to back; one host synchronisation per step)
     double* w = static_cast<double*>(W.v.p);
     for (int pass = 0; pass < 2; ++pass) {
       double* hp = dh + pass * (j + 1);
       hipLaunchKernelGGL(dots_kernel, dim3(j + 1), dim3(256), 0, s, V, L, w, j + 1, hp);
       QP_HIP(hipGetLastError());
-      hipLaunchKernelGGL(multi_axpy_kernel, dim3(blocks_for(L)), dim3(256), 0, s, V, L, hp, j + 1, -1.0, w);
+      hipLaunchKernelGGL(multi_axpy_kernel, dim3(axpy_blocks(L)), dim3(256), 0, s, V, L, hp, j + 1, -1.0, w);
       QP_HIP(hipGetLastError());
     }
-    hipLaunchKernelGGL(dots_kernel, dim3(1), dim3(256), 0, s, w, L, w, 1, dh + 2 * (j + 1));
+    double* host = columns + (j % kRing) * ring;
+    double* next = V + (int64_t)(j + 1) * L;
+    if (L <= kFusedNorm) {
+      hipLaunchKernelGGL(norm_scale_kernel, dim3(blocks_for(L)), dim3(256), 0, s, w, L, dh, 2 * (j + 1), host, next);
+    } else {
+      hipLaunchKernelGGL(dots_kernel, dim3(1), dim3(256), 0, s, w, L, w, 1, dh + 2 * (j + 1));
+      QP_HIP(hipGetLastError());
+      hipLaunchKernelGGL(scale_by_norm_kernel, dim3(blocks_for(L)), dim3(256), 0, s, w, L, dh, 2 * (j + 1), host, next);
+    }
     QP_HIP(hipGetLastError());
-    fetch(2 * (j + 1) + 1);
+    QP_HIP(hipEventRecord(c.krylov_events[j % kRing], s));
+  };
+  res.status = QPINV_ENOTCONVERGED;
+  int queued = 0;
+  for (int j = 0; j < max_iter; ++j) {
+    while (queued < max_iter && queued <= j + kAhead) enqueue(queued++);
+    QP_HIP(hipEventSynchronize(c.krylov_events[j % kRing]));
+    const double* hh = columns + (j % kRing) * ring;
     std::vector<double> col(j + 2, 0.0);
     for (int i = 0; i <= j; ++i) col[i] = hh[i] + hh[j + 1 + i];
     const double hn = std::sqrt(hh[2 * (j + 1)]);
@@ -220,9 +328,6 @@ KrylovResult gl_krylov(Ctx& c, int method, const Mat& A, const Mat& B, const Mat
       res.status = QPINV_OK;
       break;
     }
-    hipLaunchKernelGGL(scale_kernel, dim3(blocks_for(L)), dim3(256), 0, s, static_cast<const double*>(w), L, 1.0 / hn,
-                       V + (int64_t)(j + 1) * L);
-    QP_HIP(hipGetLastError());
   }
   res.iters = k;
 

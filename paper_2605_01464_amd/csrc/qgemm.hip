@@ -49,6 +49,87 @@ __global__ void __launch_bounds__(64 * WM * WN, MINW) qgemm_kernel(GemmParams<ty
   store_partials<C::NW>(P.partial, s_d, s_x, red_lds, threadIdx.x & 63, threadIdx.x >> 6, threadIdx.x);
 }
 
+// Products of at most 16 columns (a filter's output, the right-hand sides of a Krylov step).  Under 32 x 32 tiles a product of
+// 238 rows is 8 workgroups whose waves each issue all 16 plane products of their K chain.  Here a workgroup has 16 rows and its
+// wave p forms output plane p alone, the four plane products of each k in the same order, so the results are the 32 x 32
+// configuration's bit for bit from a quarter of its MFMAs.  What bounds it is that chain of dependent MFMAs (about 80 ns each).
+// Fragments come straight from global memory, PF blocks of k ahead.  FP64, 238 x 3 x 238: 45 -> 20 us; 401 x 1 x 401: 77 -> 37 us.
+template <class MM, int FLUSH, int PF>
+__global__ void __launch_bounds__(256, 1) qgemm_narrow_kernel(GemmParams<typename MM::T> P) {
+  using T = typename MM::T;
+  using VG = typename VU<T>::type;
+  constexpr int VA = V16<T>::n, KB = VA * MM::KS;
+  static_assert(MM::BLK == 16 && MM::NR == 4 && FLUSH % KB == 0, "16 x 16 MFMA");
+  __shared__ double red_lds[4][2];
+  const int tid = threadIdx.x, lane = tid & 63, p = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int fr = MM::fr(lane), fk = MM::fk(lane), m0 = blockIdx.x * 16;
+  const int64_t ra = (int64_t)min(m0 + fr, P.M - 1) * P.lda;
+  const int cb = min(fr, P.N - 1);
+  const int nb = (P.K + KB - 1) / KB;
+  // block b of KB k: plane q of A and plane p ^ q of B.  Every load is issued, from an address clamped into the matrix (no
+  // branch, so that the wait for one block does not wait for those behind it); what lies outside is zeroed when used.
+  T a[PF][4][VA], w[PF][4][VA];
+  auto load = [&](int b, T (&av)[4][VA], T (&bv)[4][VA]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int e = 0; e < VA; ++e) {
+      const int64_t k = min(b * KB + VA * fk + e, P.K - 1);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        av[q][e] = gload(P.A, q * P.psa + ra + k);
+        bv[q][e] = gload(P.B, (p ^ q) * P.psb + k * P.ldb + cb);
+      }
+    }
+  };
+  // signs of the plane products a_q b_{p ^ q} of output plane p
+  const bool n1 = p == 0 || p == 2, n2 = p == 0 || p == 3, n3 = p == 0 || p == 1;
+  typename MM::Acc acc, tot;
+#pragma unroll
+  for (int r = 0; r < MM::NR; ++r) acc[r] = tot[r] = T(0);
+  const T s1 = n1 ? T(-1) : T(1), s2 = n2 ? T(-1) : T(1), s3 = n3 ? T(-1) : T(1);
+  if (nb > 0) {
+#pragma unroll
+    for (int d = 0; d < PF; ++d) load(d, a[d], w[d]);
+  }
+  for (int b0 = 0; b0 < nb; b0 += PF) {
+#pragma unroll
+    for (int d = 0; d < PF; ++d) {
+      // blocks beyond K (the last group's) multiply zeros
+#pragma unroll
+      for (int e = 0; e < VA; ++e) {
+        const bool in = (b0 + d) * KB + VA * fk + e < P.K;
+        T x[4], y[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          x[q] = in ? a[d][q][e] : T(0);
+          y[q] = in ? w[d][q][e] : T(0);
+        }
+        acc = MM::mma(x[0], y[0], acc);
+        acc = MM::mma(s1 * x[1], y[1], acc);
+        acc = MM::mma(s2 * x[2], y[2], acc);
+        acc = MM::mma(s3 * x[3], y[3], acc);
+      }
+      load(b0 + d + PF, a[d], w[d]);
+      if constexpr (FLUSH > 0) {
+        if ((b0 + d + 1) * KB % FLUSH == 0) {
+#pragma unroll
+          for (int r = 0; r < MM::NR; ++r) {
+            tot[r] += acc[r];
+            acc[r] = T(0);
+          }
+        }
+      }
+    }
+  }
+  double s_d = 0.0, s_x = 0.0;
+  T inv[MM::NR][3];
+#pragma unroll
+  for (int r = 0; r < MM::NR; ++r) epilogue_inputs_overlap(P, p, m0 + MM::crow(lane, r), MM::ccol(lane), inv[r]);
+#pragma unroll
+  for (int r = 0; r < MM::NR; ++r)
+    epilogue_apply(P, p, m0 + MM::crow(lane, r), MM::ccol(lane), FLUSH > 0 ? tot[r] + acc[r] : acc[r], inv[r], s_d, s_x);
+  store_partials<4>(P.partial, s_d, s_x, red_lds, lane, p, tid);
+}
+
 namespace {
 struct DevLimits {
   int cus = 0;
@@ -260,9 +341,10 @@ int64_t qgemm_blocks(Prec p, int cfg, int64_t M, int64_t N) {
 int default_config(Prec p, int64_t M, int64_t N, int64_t K) {
   if (p == P_F64E || p == P_F32E) return eight_default(p, M, N, K);
   const int64_t b64 = ((M + 63) / 64) * ((N + 63) / 64);
-  if (p == P_F64) return b64 >= 1024 ? 6 : 1;
+  if (p == P_F64) return N <= 16 ? kNarrowConfig : b64 >= 1024 ? 6 : 1;
   if (p == P_BF16) return b64 >= 1024 ? 11 : b64 >= 256 ? 0 : 1;
   if (p == P_BF16X3) return ((M + 127) / 128) * ((N + 127) / 128) >= 256 ? 4 : 3;
+  if (N <= 16) return kNarrowConfig;
   return b64 >= 1024 ? 5 : 6;
 }
 
@@ -315,16 +397,29 @@ void qgemm(Prec p, const QView& A, const QView& B, int64_t M, int64_t N, int64_t
   if (epi.reduce && (!red || epi.ref >= epi.nin)) throw Error(-1, "qgemm: bad reduction");
   if (cfg < 0) cfg = default_config(p, M, N, K);
   const auto& cfgs = tile_configs(p);
-  if (cfg >= (int)cfgs.size()) throw Error(-1, "qgemm: bad tile config");
+  const bool narrow = cfg == kNarrowConfig && (p == P_F64 || p == P_F32) && N <= 16;
+  if (cfg >= (int)cfgs.size() && !narrow) throw Error(-1, "qgemm: bad tile config");
   // an upper bound of the workgroups launched (a per-CU configuration launches at most this many)
-  const int64_t nb = p == P_BF16     ? bf16_blocks(cfg, M, N)
+  const int64_t nb = narrow          ? (M + 15) / 16
+                     : p == P_BF16     ? bf16_blocks(cfg, M, N)
                      : p == P_BF16X3 ? bf16x3_blocks(cfg, M, N)
                                      : blocks_for(cfgs[cfg], M, N);
   if (epi.reduce && nb > scratch.capacity / 2) throw Error(-1, "qgemm: reduction scratch too small");
   double* partial = epi.reduce ? scratch.partial : nullptr;
   int64_t launched = 0;
   if ((p == P_F64E || p == P_F32E) && !eight_fits(p, A, B, M, K)) throw Error(-1, "qgemm: operands of the eight-product form");
-  if (p == P_F64E) {
+  if (narrow) {
+    launched = M == 0 || N == 0 ? 0 : nb;
+    if (launched > 0) {
+      if (p == P_F64)
+        hipLaunchKernelGGL((qgemm_narrow_kernel<MM16D, 0, 3>), dim3((unsigned)nb), dim3(256), 0, stream,
+                           make_params<double>(A, B, M, N, K, epi, partial));
+      else
+        hipLaunchKernelGGL((qgemm_narrow_kernel<MM16F, 128, 1>), dim3((unsigned)nb), dim3(256), 0, stream,
+                           make_params<float>(A, B, M, N, K, epi, partial));
+      QP_HIP(hipGetLastError());
+    }
+  } else if (p == P_F64E) {
     launched = f64x8_launch(make_params<double>(A, B, M, N, K, epi, partial), cfg, stream);
   } else if (p == P_F32E) {
     launched = f32x8_launch(make_params<float>(A, B, M, N, K, epi, partial), cfg, stream);

@@ -67,6 +67,9 @@ LaunchShape launch_shape(int64_t tiles, int per_cu, int occ, size_t static_lds);
 // F64 takes double storage).
 const std::vector<TileConfig>& tile_configs(Prec p);
 
+// The form for at most 16 columns (qgemm_narrow_kernel), outside the tables; its number in the product statistics
+constexpr int kNarrowConfig = 63;
+
 // Heuristic choice of tile configuration for a shape (used when no tuned choice exists).
 int default_config(Prec p, int64_t M, int64_t N, int64_t K);
 

@@ -40,18 +40,6 @@ __device__ __forceinline__ void planes_of(const T (&P)[8], T (&c)[4]) {
   c[3] = T(0.5) * (g + d) - P[7];
 }
 
-// Sixteen bytes at an address aligned to the element only (global loads take any such address).
-template <class T>
-struct VU;
-template <>
-struct VU<float> {
-  typedef float type __attribute__((ext_vector_type(4), aligned(4)));
-};
-template <>
-struct VU<double> {
-  typedef double type __attribute__((ext_vector_type(2), aligned(8)));
-};
-
 // ------------------------------------------------------------------------------------------------
 // Tiles staged through LDS, from operands whose rows are 16-byte aligned.  A thread loads the four planes of one 16-byte chunk
 // and writes its eight sums to LDS, so the waves run eight plain products: the sums share the matrix core's FP64 unit, and

@@ -61,6 +61,18 @@ struct V16<double> {
   static constexpr int n = 2;
 };
 
+// Sixteen bytes at an address aligned to the element only (global loads take any such address).
+template <class T>
+struct VU;
+template <>
+struct VU<float> {
+  typedef float type __attribute__((ext_vector_type(4), aligned(4)));
+};
+template <>
+struct VU<double> {
+  typedef double type __attribute__((ext_vector_type(2), aligned(8)));
+};
+
 template <class T>
 struct GemmParams {
   const T* A;
@@ -180,7 +192,10 @@ __device__ __forceinline__ void epilogue_apply(const GemmParams<T>& P, int p, in
 #pragma unroll
   for (int t = 0; t < 3; ++t) {
     if (t < P.nout) {
-      const T o = P.ca[t] * v + P.cg[t] * eye + P.cb[t][0] * inv[0] + P.cb[t][1] * inv[1] + P.cb[t][2] * inv[2];
+      // written out as multiply-adds: contracted by the compiler, kernels whose sums agree could differ here
+      T o = fma(P.cg[t], eye, P.ca[t] * v);
+#pragma unroll
+      for (int u = 0; u < 3; ++u) o = fma(P.cb[t][u], inv[u], o);
       gstore(P.out[t], p * P.pso[t] + (int64_t)row * P.ldo[t] + col, o);
       if (t == 0 && P.reduce) {
         const double od = (double)o;

@@ -130,6 +130,8 @@ Ctx::~Ctx() {
   if (scratch.partial) (void)hipFree(scratch.partial);
   if (scratch.stage) (void)hipFree(scratch.stage);
   if (dsc) (void)hipFree(dsc);
+  if (krylov_buf) (void)hipHostFree(krylov_buf);
+  for (hipEvent_t e : krylov_events) (void)hipEventDestroy(e);
   if (hsc) (void)hipHostFree(hsc);
   if (hstage) (void)hipHostFree(hstage);
 }
@@ -139,8 +141,9 @@ int Ctx::config_for(Prec p, int64_t M, int64_t N, int64_t K, hipStream_t s) {
   auto key = std::make_tuple((int)p, M, N, K);
   auto it = tuned.find(key);
   if (it != tuned.end()) return it->second;
-  if (opt.autotune && !no_alloc) return autotune(*this, p, M, N, K, nullptr, s);
-  return default_config(p, M, N, K);
+  const int def = default_config(p, M, N, K);
+  if (def != kNarrowConfig && opt.autotune && !no_alloc) return autotune(*this, p, M, N, K, nullptr, s);
+  return def;
 }
 
 Mat from_abi(const qpinv_qmat& q) {
@@ -1552,7 +1555,8 @@ int autotune(Ctx& c, Prec p, int64_t M, int64_t N, int64_t K, double* best_ms, h
   hipEvent_t e0, e1;
   QP_HIP(hipEventCreate(&e0));
   QP_HIP(hipEventCreate(&e1));
-  int best = default_config(p, M, N, K);
+  const bool narrow = default_config(p, M, N, K) == kNarrowConfig;  // stays the choice where it applies: no tile is faster
+  int best = 0;
   double best_t = 1e300;
   // two timed rounds over all configurations (the first also warms clocks and caches); a
   // configuration's time is its faster round
@@ -1579,7 +1583,7 @@ int autotune(Ctx& c, Prec p, int64_t M, int64_t N, int64_t K, double* best_ms, h
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
-  c.tuned[std::make_tuple((int)p, M, N, K)] = best;
+  if (!narrow) c.tuned[std::make_tuple((int)p, M, N, K)] = best;
   if (best_ms) *best_ms = best_t;
   return best;
 }

@@ -78,6 +78,9 @@ struct Ctx {
   unsigned int small_bar_base = 0;  // the arrival count those barrier words hold
   void* small_params_dev = nullptr;         // the small solve's parameter block in device memory, and
   std::vector<unsigned char> small_params;  // the bytes it holds (copied again only when they change)
+  double* krylov_buf = nullptr;  // pinned columns of a Krylov run (krylov.hip), krylov_cap doubles, and their events
+  size_t krylov_cap = 0;
+  std::vector<hipEvent_t> krylov_events;
   double flops = 0.0;  // running count of algorithmic product flops
   // event pairs around product launches (option gemm_timing)
   std::vector<std::pair<hipEvent_t, hipEvent_t>> events;
