@@ -18,14 +18,14 @@ __global__ void __launch_bounds__(64 * WM * WN, MINW) qgemm8_kernel(GemmParams<t
   store_partials<C::NW>(P.partial, s_d, s_x, red_lds, threadIdx.x & 63, threadIdx.x >> 6, threadIdx.x);
 }
 
-template <class MM, int TM, int TN, int NWV, int MINW>
+template <class MM, int TM, int TN, int NWV, int PF, int MINW>
 __global__ void __launch_bounds__(64 * NWV, MINW) qgemm8_regs_kernel(GemmParams<typename MM::T> P) {
   __shared__ __attribute__((aligned(16))) typename MM::T smem[NWV * 4 * 256 * TM * TN];
   __shared__ double red_lds[NWV][2];
   double s_d = 0.0, s_x = 0.0;
   int tm, tn;
   tile_of_block(blockIdx.x, P.tiles_m * P.tiles_n, P.tiles_m, P.tiles_n, tm, tn);
-  gemm8_regs_tile<MM, TM, TN, NWV>(P, tm, tn, smem, s_d, s_x);
+  gemm8_regs_tile<MM, TM, TN, NWV, PF>(P, tm, tn, smem, s_d, s_x);
   store_partials<NWV>(P.partial, s_d, s_x, red_lds, threadIdx.x & 63, threadIdx.x >> 6, threadIdx.x);
 }
 
@@ -42,14 +42,14 @@ static int64_t launch8(const GemmParams<typename MM::T>& P0, hipStream_t s) {
   return nt;
 }
 
-template <class MM, int TM, int TN, int NWV, int MINW>
+template <class MM, int TM, int TN, int NWV, int PF, int MINW>
 static int64_t launch8_regs(const GemmParams<typename MM::T>& P0, hipStream_t s) {
   GemmParams<typename MM::T> P = P0;
   P.tiles_m = (P.M + 16 * TM - 1) / (16 * TM);
   P.tiles_n = (P.N + 16 * TN - 1) / (16 * TN);
   const int64_t nt = (int64_t)P.tiles_m * P.tiles_n;
   if (nt == 0) return 0;
-  hipLaunchKernelGGL((qgemm8_regs_kernel<MM, TM, TN, NWV, MINW>), dim3((unsigned)nt), dim3(64 * NWV), 0, s, P);
+  hipLaunchKernelGGL((qgemm8_regs_kernel<MM, TM, TN, NWV, PF, MINW>), dim3((unsigned)nt), dim3(64 * NWV), 0, s, P);
   QP_HIP(hipGetLastError());
   return nt;
 }
@@ -61,12 +61,12 @@ struct Entry8 {
 };
 
 // Three tiles each: 64 x 64 (8 waves, one workgroup per compute unit) and 32 x 32 (4 waves, two per unit) through LDS, and
-// 16 x 16 in registers (4 waves, each every fourth block of k; two workgroups per unit in FP64, three in FP32).
+// 16 x 16 in registers (4 waves, each every fourth block of k; three workgroups per unit in FP64, four in FP32).
 static const std::vector<Entry8<double>>& f64_table8() {
   static const std::vector<Entry8<double>> t = {
       {{0, 64, 64, 8, 512, "f64x8_64x64_w2x4"}, launch8<MM16D, 64, 64, 2, 4, 0, 2>},
       {{1, 32, 32, 8, 256, "f64x8_32x32_w2x2"}, launch8<MM16D, 32, 32, 2, 2, 0, 2>},
-      {{2, 16, 16, 8, 256, "f64x8_16x16_regs4"}, launch8_regs<MM16D, 1, 1, 4, 2>},
+      {{2, 16, 16, 8, 256, "f64x8_16x16_regs4"}, launch8_regs<MM16D, 1, 1, 4, 1, 3>},
   };
   return t;
 }
@@ -77,7 +77,7 @@ static const std::vector<Entry8<float>>& f32_table8() {
   static const std::vector<Entry8<float>> t = {
       {{0, 64, 64, 16, 1024, "f32x8_64x64_w4x4"}, launch8<MM16F, 64, 64, 4, 4, 128, 4>},
       {{1, 32, 32, 16, 256, "f32x8_32x32_w2x2"}, launch8<MM16F, 32, 32, 2, 2, 128, 2>},
-      {{2, 16, 16, 16, 256, "f32x8_16x16_regs4"}, launch8_regs<MM16F, 1, 1, 4, 3>},
+      {{2, 16, 16, 16, 256, "f32x8_16x16_regs4"}, launch8_regs<MM16F, 1, 1, 4, 1, 4>},
   };
   return t;
 }
@@ -95,19 +95,19 @@ const std::vector<TileConfig>& eight_configs(Prec p) {
 
 // The tile that takes the least time by a model of rounds: with `cap` workgroups resident on the chip, every full round costs
 // full x K microseconds and the last, partial one `part` x K if it leaves at most one workgroup per unit.  Measured, FP64 (us):
-//   K = 300, 300 x 300:    64 x 64 91    32 x 32 36    16 x 16 21     (direct form 55)
-//   K = 1000, 500 x 500:   64 x 64 268   32 x 32 107   16 x 16 101    (170)
-//   K = 700, 700 x 700:    64 x 64 197   32 x 32 132   16 x 16 156    (204)
+//   K = 300, 300 x 300:    64 x 64 91    32 x 32 36    16 x 16 19     (direct form 55)
+//   K = 1000, 500 x 500:   64 x 64 268   32 x 32 107   16 x 16 95     (170)
+//   K = 700, 700 x 700:    64 x 64 197   32 x 32 131   16 x 16 142    (204)
 //   K = 1000, 1000 x 1000: 64 x 64 304   32 x 32 364   16 x 16 415    (564)
 //   K = 4096, 4096 x 4096: 64 x 64 17089 32 x 32 20071                (30600; 64.3 TFLOP/s of MFMA work)
-// and FP32: 300^3 49 / 23 / 14 (41), 700^3 107 / 74 / 88 (138), 1000^3 163 / 200 / 251 (326), 4096^3 8863 / 10760 (15931).
+// and FP32: 300^3 49 / 23 / 12 (41), 700^3 107 / 74 / 76 (138), 1000^3 163 / 200 / 251 (326), 4096^3 8863 / 10760 (15931).
 int eight_default(Prec p, int64_t M, int64_t N, int64_t K) {
   struct Cost {
     int64_t tile, cap;
     double full, part, fixed;
   };
-  static constexpr Cost k64[3] = {{64, 256, 0.27, 0.27, 12}, {32, 512, 0.175, 0.1, 6}, {16, 512, 0.053, 0.025, 3}};
-  static constexpr Cost k32[3] = {{64, 256, 0.14, 0.14, 10}, {32, 512, 0.1, 0.062, 5}, {16, 768, 0.049, 0.017, 3}};
+  static constexpr Cost k64[3] = {{64, 256, 0.27, 0.27, 12}, {32, 512, 0.175, 0.1, 6}, {16, 512, 0.05, 0.025, 3}};
+  static constexpr Cost k32[3] = {{64, 256, 0.14, 0.14, 10}, {32, 512, 0.1, 0.062, 5}, {16, 768, 0.041, 0.017, 3}};
   int best = 0;
   double best_t = 0.0;
   for (int i = 0; i < 3; ++i) {

@@ -295,7 +295,7 @@ __device__ __forceinline__ void gemm8_tile(const GemmParams<typename MM::T>& P, 
 // straight to registers in MFMA layout (no LDS, no barrier in the K loop), the sums are formed there, and the waves'
 // planes meet once in LDS, where each thread sums its outputs in wave order and writes them.
 // ------------------------------------------------------------------------------------------------
-template <class MM, int TM, int TN, int NWV>
+template <class MM, int TM, int TN, int NWV, int PF>
 __device__ __forceinline__ void gemm8_regs_tile(const GemmParams<typename MM::T>& P, int tm, int tn, typename MM::T* smem,
                                                 double& s_d, double& s_x) {
   using T = typename MM::T;
@@ -303,7 +303,7 @@ __device__ __forceinline__ void gemm8_regs_tile(const GemmParams<typename MM::T>
   using VG = typename VU<T>::type;
   constexpr int VA = V16<T>::n, KB = VA * MM::KS, BM = 16 * TM, BN = 16 * TN;
   static_assert(MM::BLK == 16 && MM::NR == 4, "16 x 16 MFMA");
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int fr = MM::fr(lane), fk = MM::fk(lane);
   const int m0 = tm * BM, n0 = tn * BN;
   Acc acc[8][TM][TN];
@@ -316,68 +316,73 @@ __device__ __forceinline__ void gemm8_regs_tile(const GemmParams<typename MM::T>
 #pragma unroll
         for (int r = 0; r < MM::NR; ++r) acc[t][i][j][r] = T(0);
 
-  // row / column offsets of the lane's fragments, clamped into the matrix (outputs outside are not written)
-  int64_t ra[TM];
-  int cb[TN];
+  // Block `kb` of the wave's share starts at k = (kb NWV + w) KB.  Every load is issued, PF blocks ahead, from an address clamped
+  // into the matrix: under a branch the wait for one block would be one for the blocks behind it too.  Addresses are a uniform
+  // base (plane and block) and a lane offset that only the last block changes.  (Rows and columns outside the matrix only reach
+  // outputs that are not written.)
+  const int nb = (P.K + KB - 1) / KB, mine = (nb - w + NWV - 1) / NWV;
+  unsigned ra[TM], cb[TN];
 #pragma unroll
-  for (int i = 0; i < TM; ++i) ra[i] = (int64_t)min(m0 + 16 * i + fr, P.M - 1) * P.lda;
+  for (int i = 0; i < TM; ++i) ra[i] = (unsigned)min(m0 + 16 * i + fr, P.M - 1) * (unsigned)P.lda;
 #pragma unroll
-  for (int j = 0; j < TN; ++j) cb[j] = min(n0 + 16 * j + fr, P.N - 1);
-
-  T a[TM][4][VA], b[TN][4][VA];
-  auto load = [&](int k0) {
-    const int gk = k0 + VA * fk;
-    if (k0 + KB <= P.K) {
+  for (int j = 0; j < TN; ++j) cb[j] = (unsigned)min(n0 + 16 * j + fr, P.N - 1);
+  T a[PF][TM][4][VA], b[PF][TN][4][VA];
+  auto load = [&](int kb, int d) __attribute__((always_inline)) {
+    const int k0 = min((kb * NWV + w) * KB, (nb - 1) * KB);
+    unsigned ka = VA * fk, kr[VA];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
+    for (int e = 0; e < VA; ++e) kr[e] = VA * fk + e;
+    if (k0 + KB > P.K) {
+      ka = min(ka, (unsigned)(((P.K - 1) / VA) * VA - k0));
 #pragma unroll
-        for (int i = 0; i < TM; ++i) {
-          const VG v = gload(reinterpret_cast<const VG*>(P.A + q * P.psa + ra[i] + gk), 0);
+      for (int e = 0; e < VA; ++e) kr[e] = min(kr[e], (unsigned)(P.K - 1 - k0));
+    }
 #pragma unroll
-          for (int e = 0; e < VA; ++e) a[i][q][e] = v[e];
-        }
+    for (int q = 0; q < 4; ++q) {
+      const char* const pa = reinterpret_cast<const char*>(P.A + q * P.psa + k0);
+      const char* const pb = reinterpret_cast<const char*>(P.B + q * P.psb + (int64_t)k0 * P.ldb);
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
+      for (int i = 0; i < TM; ++i) {
+        const VG v = gload(reinterpret_cast<const VG*>(pa + (uint32_t)((ra[i] + ka) * (unsigned)sizeof(T))), 0);
 #pragma unroll
-          for (int e = 0; e < VA; ++e) b[j][q][e] = gload(P.B, q * P.psb + (int64_t)(gk + e) * P.ldb + cb[j]);
+        for (int e = 0; e < VA; ++e) a[d][i][q][e] = v[e];
       }
-    } else {  // the last block of a K that is no multiple of KB: element loads, zeros outside
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int e = 0; e < VA; ++e)
+          b[d][j][q][e] = gload(
+              reinterpret_cast<const T*>(pb + (uint32_t)((kr[e] * (unsigned)P.ldb + cb[j]) * (unsigned)sizeof(T))), 0);
+    }
+  };
+  auto block = [&](int kb, int d) __attribute__((always_inline)) {
+    const int k0 = (kb * NWV + w) * KB;
+    if (k0 + KB > P.K) {  // zeros outside
 #pragma unroll
       for (int e = 0; e < VA; ++e) {
-        const bool in = gk + e < P.K;
-        const int k = in ? gk + e : P.K - 1;
+        const bool in = k0 + VA * fk + e < P.K;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
 #pragma unroll
-          for (int i = 0; i < TM; ++i) {
-            const T v = gload(P.A, q * P.psa + ra[i] + k);
-            a[i][q][e] = in ? v : T(0);
-          }
+          for (int i = 0; i < TM; ++i) a[d][i][q][e] = in ? a[d][i][q][e] : T(0);
 #pragma unroll
-          for (int j = 0; j < TN; ++j) {
-            const T v = gload(P.B, q * P.psb + (int64_t)k * P.ldb + cb[j]);
-            b[j][q][e] = in ? v : T(0);
-          }
+          for (int j = 0; j < TN; ++j) b[d][j][q][e] = in ? b[d][j][q][e] : T(0);
         }
       }
     }
-  };
-  int k0 = w * KB;
-  if (k0 < P.K) load(k0);
-  while (k0 < P.K) {
     T l[TM][VA][8], r8[TN][VA][8];
 #pragma unroll
     for (int e = 0; e < VA; ++e)
 #pragma unroll
       for (int t = 0; t < 8; ++t) {
 #pragma unroll
-        for (int i = 0; i < TM; ++i) l[i][e][t] = sum8(t, a[i][0][e], a[i][1][e], a[i][2][e], a[i][3][e]);
+        for (int i = 0; i < TM; ++i) l[i][e][t] = sum8(t, a[d][i][0][e], a[d][i][1][e], a[d][i][2][e], a[d][i][3][e]);
 #pragma unroll
         for (int j = 0; j < TN; ++j)
-          r8[j][e][t] = sum8(b_sum(t), b[j][b_plane(0)][e], b[j][b_plane(1)][e], b[j][b_plane(2)][e], b[j][b_plane(3)][e]);
+          r8[j][e][t] = sum8(b_sum(t), b[d][j][b_plane(0)][e], b[d][j][b_plane(1)][e], b[d][j][b_plane(2)][e],
+                             b[d][j][b_plane(3)][e]);
       }
-    k0 += NWV * KB;
-    if (k0 < P.K) load(k0);  // the next block's loads run behind this block's MFMAs
+    load(kb + PF, d);
 #pragma unroll
     for (int t = 0; t < 8; ++t)
 #pragma unroll
@@ -386,6 +391,15 @@ __device__ __forceinline__ void gemm8_regs_tile(const GemmParams<typename MM::T>
         for (int i = 0; i < TM; ++i)
 #pragma unroll
           for (int j = 0; j < TN; ++j) acc[t][i][j] = MM::mma(l[i][e][t], r8[j][e][t], acc[t][i][j]);
+  };
+  if (mine > 0) {
+#pragma unroll
+    for (int d = 0; d < PF; ++d) load(d, d);
+  }
+  for (int kb = 0; kb < mine; kb += PF) {
+#pragma unroll
+    for (int d = 0; d < PF; ++d)
+      if (d == 0 || kb + d < mine) block(kb + d, d);
   }
 
   // each wave's planes to LDS as [wave][plane][BM][BN]
