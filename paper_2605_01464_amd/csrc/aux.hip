@@ -207,29 +207,60 @@ __global__ void __launch_bounds__(256) norms_row_kernel(const T* __restrict__ A,
   }
 }
 
-template <class T>
+// Column passes (here and in the power iteration): a workgroup has CW columns of one row block, its CG groups of threads
+// taking every CG-th row.  With 256 columns a workgroup a 401-column matrix was 14 of them, each walking 58 rows one
+// after the other (gemv_h 17 us, norms_col 23); with 32 columns and 8 rows at a time the chip has 91 (5 and 6).  Where 256
+// columns give at least two workgroups per unit they stay, for their longer rows (4096^2 FP32 gemv_h 45 against 71 us).
+static bool wide_columns(int64_t n, int nrb) { return ((n + 255) / 256) * nrb >= 512; }
+
+template <class T, int CW>
 __global__ void __launch_bounds__(256) norms_col_kernel(const T* __restrict__ A, int64_t lda, int64_t psa, int m, int n,
                                                         double* __restrict__ col_part) {
-  const int j = blockIdx.x * 256 + threadIdx.x;
+  constexpr int CG = 256 / CW;
+  __shared__ double sh[CG][CW];
+  const int c = threadIdx.x % CW, g = threadIdx.x / CW, j = blockIdx.x * CW + c;
   const int rb = blockIdx.y, nrb = gridDim.y;
   const int per = (m + nrb - 1) / nrb;
   const int r0 = rb * per, r1 = min(m, r0 + per);
-  if (j >= n) return;
   double sa = 0.0;
-  for (int i = r0; i < r1; ++i) {
-    double q2 = 0.0;
-    for (int p = 0; p < 4; ++p) {
-      const double v = (double)A[p * psa + (int64_t)i * lda + j];
-      q2 += v * v;
+  if (j < n) {
+    for (int i = r0 + g; i < r1; i += CG) {
+      double q2 = 0.0;
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        const double v = (double)A[p * psa + (int64_t)i * lda + j];
+        q2 += v * v;
+      }
+      sa += sqrt(q2);
     }
-    sa += sqrt(q2);
   }
-  col_part[(int64_t)rb * n + j] = sa;
+  sh[g][c] = sa;
+  __syncthreads();
+  if (g == 0 && j < n) {
+    for (int q = 1; q < CG; ++q) sa += sh[q][c];
+    col_part[(int64_t)rb * n + j] = sa;
+  }
+}
+
+// the column sums of one block of 256 columns and their maximum, for matrices of more than kFinalCols columns
+constexpr int kFinalCols = 512;
+__global__ void __launch_bounds__(256) norms_colmax_kernel(const double* __restrict__ col_part, int n, int nrb,
+                                                           double* __restrict__ cmax) {
+  __shared__ double sh[256];
+  const int j = blockIdx.x * 256 + threadIdx.x;
+  double c = 0.0;
+  if (j < n) {
+#pragma unroll 8
+    for (int rb = 0; rb < nrb; ++rb) c += col_part[(int64_t)rb * n + j];
+  }
+  c = block_max256(c, sh);
+  if (threadIdx.x == 0) cmax[blockIdx.x] = c;
 }
 
 __global__ void __launch_bounds__(256) norms_final_kernel(const double* __restrict__ row_abs, const double* __restrict__ row_sq,
                                                           const double* __restrict__ row_nf, const double* __restrict__ col_part,
-                                                          int m, int n, int nrb, double* __restrict__ out) {
+                                                          int m, int n, int nrb, const double* __restrict__ cmax_part,
+                                                          int ncmax, double* __restrict__ out) {
   __shared__ double sh[256];
   double fro = 0.0, rmax = 0.0, nf = 0.0, cmax = 0.0;
   for (int i = threadIdx.x; i < m; i += 256) {
@@ -237,10 +268,14 @@ __global__ void __launch_bounds__(256) norms_final_kernel(const double* __restri
     rmax = fmax(rmax, row_abs[i]);
     nf += row_nf[i];
   }
-  for (int j = threadIdx.x; j < n; j += 256) {
-    double c = 0.0;
-    for (int rb = 0; rb < nrb; ++rb) c += col_part[(int64_t)rb * n + j];
-    cmax = fmax(cmax, c);
+  if (ncmax > 0) {
+    for (int j = threadIdx.x; j < ncmax; j += 256) cmax = fmax(cmax, cmax_part[j]);
+  } else {
+    for (int j = threadIdx.x; j < n; j += 256) {
+      double c = 0.0;
+      for (int rb = 0; rb < nrb; ++rb) c += col_part[(int64_t)rb * n + j];
+      cmax = fmax(cmax, c);
+    }
   }
   fro = block_sum256(fro, sh);
   nf = block_sum256(nf, sh);
@@ -254,7 +289,9 @@ __global__ void __launch_bounds__(256) norms_final_kernel(const double* __restri
   }
 }
 
-int64_t norms_work_doubles(int64_t m, int64_t n) { return 3 * m + (int64_t)col_row_blocks(m) * n + 8; }
+int64_t norms_work_doubles(int64_t m, int64_t n) {
+  return 3 * m + (int64_t)col_row_blocks(m) * n + std::max<int64_t>(8, (n + 255) / 256);
+}
 
 template <class T>
 void norms(const QView& A, int64_t m, int64_t n, double* out, double* work, hipStream_t s) {
@@ -270,11 +307,19 @@ void norms(const QView& A, int64_t m, int64_t n, double* out, double* work, hipS
   hipLaunchKernelGGL((norms_row_kernel<T>), dim3((unsigned)m), dim3(256), 0, s, static_cast<const T*>(A.p), A.ld, A.ps,
                      (int)n, row_abs, row_sq, row_nf);
   QP_HIP(hipGetLastError());
-  hipLaunchKernelGGL((norms_col_kernel<T>), dim3((unsigned)((n + 255) / 256), (unsigned)nrb), dim3(256), 0, s,
-                     static_cast<const T*>(A.p), A.ld, A.ps, (int)m, (int)n, col_part);
+  if (wide_columns(n, nrb))
+    hipLaunchKernelGGL((norms_col_kernel<T, 256>), dim3((unsigned)((n + 255) / 256), (unsigned)nrb), dim3(256), 0, s,
+                       static_cast<const T*>(A.p), A.ld, A.ps, (int)m, (int)n, col_part);
+  else
+    hipLaunchKernelGGL((norms_col_kernel<T, 32>), dim3((unsigned)((n + 31) / 32), (unsigned)nrb), dim3(256), 0, s,
+                       static_cast<const T*>(A.p), A.ld, A.ps, (int)m, (int)n, col_part);
   QP_HIP(hipGetLastError());
+  double* const cmax = col_part + (int64_t)nrb * n;
+  const int ncmax = n > kFinalCols ? (int)((n + 255) / 256) : 0;
+  if (ncmax > 0)
+    hipLaunchKernelGGL(norms_colmax_kernel, dim3((unsigned)ncmax), dim3(256), 0, s, col_part, (int)n, nrb, cmax);
   hipLaunchKernelGGL(norms_final_kernel, dim3(1), dim3(256), 0, s, row_abs, row_sq, row_nf, col_part, (int)m, (int)n, nrb,
-                     out);
+                     cmax, ncmax, out);
   QP_HIP(hipGetLastError());
 }
 
@@ -311,15 +356,27 @@ __global__ void __launch_bounds__(256) sumsq_kernel(const double* __restrict__ x
   }
 }
 
-// w_i = (A v)_i / sqrt(*vn2): one workgroup per row.  v and w are plane-major (4 x len).
-template <class T>
+__device__ __forceinline__ double wave_sum64(double x) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
+  return x;
+}
+
+// w_i = (A v)_i / ||v||, v and w plane-major (4 x len).  ||v||^2 is summed from the elements a row's product reads anyway
+// (the same value in the same order for every row), which saves a launch a step.  A row is a wave's (WG = false) or, from
+// kWideRows columns on, a workgroup's: the five sums of a workgroup cost forty barriers, a third of a 400-column row's time,
+// but four waves at one row keep fewer rows open, whose plane and row strides are powers of two in the large cases
+// (4096^2 FP32: 60 us with a workgroup a row, 106 with a wave, 179 with a wave for two rows).
+constexpr int64_t kWideRows = 1024;
+template <class T, bool WG>
 __global__ void __launch_bounds__(256) gemv_n_kernel(const T* __restrict__ A, int64_t lda, int64_t psa, int m, int n,
-                                                     const double* __restrict__ v, const double* __restrict__ vn2,
-                                                     double* __restrict__ w) {
+                                                     const double* __restrict__ v, double* __restrict__ w) {
   __shared__ double sh[256];
-  const int i = blockIdx.x;
-  double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-  for (int j = threadIdx.x; j < n; j += 256) {
+  const int i = WG ? blockIdx.x : blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int first = WG ? threadIdx.x : threadIdx.x & 63;
+  if (i >= m) return;
+  double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0, vv = 0.0;
+  for (int j = first; j < n; j += WG ? 256 : 64) {
     const int64_t o = (int64_t)i * lda + j;
     const double as = A[o], ax = A[psa + o], ay = A[2 * psa + o], az = A[3 * psa + o];
     const double vs = v[j], vx = v[n + j], vy = v[2 * n + j], vz = v[3 * n + j];
@@ -327,13 +384,16 @@ __global__ void __launch_bounds__(256) gemv_n_kernel(const T* __restrict__ A, in
     s1 += as * vx + ax * vs + ay * vz - az * vy;
     s2 += as * vy - ax * vz + ay * vs + az * vx;
     s3 += as * vz + ax * vy - ay * vx + az * vs;
+    vv += vs * vs + vx * vx + vy * vy + vz * vz;
   }
-  s0 = block_sum256(s0, sh);
-  s1 = block_sum256(s1, sh);
-  s2 = block_sum256(s2, sh);
-  s3 = block_sum256(s3, sh);
-  if (threadIdx.x == 0) {
-    const double inv = 1.0 / sqrt(vn2[0]);
+  auto total = [&](double x) { return WG ? block_sum256(x, sh) : wave_sum64(x); };
+  s0 = total(s0);
+  s1 = total(s1);
+  s2 = total(s2);
+  s3 = total(s3);
+  vv = total(vv);
+  if (first == 0) {
+    const double inv = 1.0 / sqrt(vv);
     w[i] = s0 * inv;
     w[m + i] = s1 * inv;
     w[2 * m + i] = s2 * inv;
@@ -342,29 +402,38 @@ __global__ void __launch_bounds__(256) gemv_n_kernel(const T* __restrict__ A, in
 }
 
 // partial z_j = sum_{i in row block} conj(a_ij) w_i
-template <class T>
+template <class T, int CW>
 __global__ void __launch_bounds__(256) gemv_h_kernel(const T* __restrict__ A, int64_t lda, int64_t psa, int m, int n,
                                                      const double* __restrict__ w, double* __restrict__ zpart) {
-  const int j = blockIdx.x * 256 + threadIdx.x;
+  constexpr int CG = 256 / CW;
+  __shared__ double sh[CG][4][CW];
+  const int c = threadIdx.x % CW, g = threadIdx.x / CW, j = blockIdx.x * CW + c;
   const int rb = blockIdx.y, nrb = gridDim.y;
   const int per = (m + nrb - 1) / nrb;
   const int r0 = rb * per, r1 = min(m, r0 + per);
-  if (j >= n) return;
   double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-  for (int i = r0; i < r1; ++i) {
-    const int64_t o = (int64_t)i * lda + j;
-    const double as = A[o], ax = A[psa + o], ay = A[2 * psa + o], az = A[3 * psa + o];
-    const double ws = w[i], wx = w[m + i], wy = w[2 * m + i], wz = w[3 * m + i];
-    s0 += as * ws + ax * wx + ay * wy + az * wz;
-    s1 += as * wx - ax * ws - ay * wz + az * wy;
-    s2 += as * wy + ax * wz - ay * ws - az * wx;
-    s3 += as * wz - ax * wy + ay * wx - az * ws;
+  if (j < n) {
+    for (int i = r0 + g; i < r1; i += CG) {
+      const int64_t o = (int64_t)i * lda + j;
+      const double as = A[o], ax = A[psa + o], ay = A[2 * psa + o], az = A[3 * psa + o];
+      const double ws = w[i], wx = w[m + i], wy = w[2 * m + i], wz = w[3 * m + i];
+      s0 += as * ws + ax * wx + ay * wy + az * wz;
+      s1 += as * wx - ax * ws - ay * wz + az * wy;
+      s2 += as * wy + ax * wz - ay * ws - az * wx;
+      s3 += as * wz - ax * wy + ay * wx - az * ws;
+    }
   }
-  double* zp = zpart + (int64_t)rb * 4 * n;
-  zp[j] = s0;
-  zp[n + j] = s1;
-  zp[2 * n + j] = s2;
-  zp[3 * n + j] = s3;
+  sh[g][0][c] = s0;
+  sh[g][1][c] = s1;
+  sh[g][2][c] = s2;
+  sh[g][3][c] = s3;
+  __syncthreads();
+  for (int e = threadIdx.x; e < 4 * CW; e += 256) {  // (plane, column)
+    const int p = e / CW, col = blockIdx.x * CW + e % CW;
+    double a = 0.0;
+    for (int q = 0; q < CG; ++q) a += sh[q][p][e % CW];
+    if (col < n) zpart[(int64_t)rb * 4 * n + (int64_t)p * n + col] = a;
+  }
 }
 
 __global__ void __launch_bounds__(256) sum_parts_kernel(const double* __restrict__ part, int nrb, int64_t len,
@@ -372,6 +441,7 @@ __global__ void __launch_bounds__(256) sum_parts_kernel(const double* __restrict
   const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (e >= len) return;
   double a = 0.0;
+#pragma unroll 8
   for (int rb = 0; rb < nrb; ++rb) a += part[(int64_t)rb * len + e];
   out[e] = a;
 }
@@ -393,19 +463,29 @@ void power_sigma1_sq(const QView& A, int64_t m, int64_t n, int steps, uint64_t s
   double* w = v + 4 * n;
   double* zpart = w + 4 * m;
   const int nrb = col_row_blocks(m);
-  double* vn2 = zpart + (int64_t)nrb * 4 * n;
   const T* Ap = static_cast<const T*>(A.p);
   hipLaunchKernelGGL(power_init_kernel, dim3((unsigned)((4 * n + 255) / 256)), dim3(256), 0, s, v, (int)n, (uint64_t)seed);
   QP_HIP(hipGetLastError());
   for (int k = 0; k < steps; ++k) {
-    hipLaunchKernelGGL(sumsq_kernel, dim3(1), dim3(256), 0, s, v, 4 * n, vn2, (double*)nullptr);
-    hipLaunchKernelGGL((gemv_n_kernel<T>), dim3((unsigned)m), dim3(256), 0, s, Ap, A.ld, A.ps, (int)m, (int)n, v, vn2, w);
-    hipLaunchKernelGGL(sumsq_kernel, dim3(1), dim3(256), 0, s, w, 4 * m, lambda, k > 0 ? lambda + 1 : (double*)nullptr);
-    hipLaunchKernelGGL((gemv_h_kernel<T>), dim3((unsigned)((n + 255) / 256), (unsigned)nrb), dim3(256), 0, s, Ap, A.ld,
-                       A.ps, (int)m, (int)n, w, zpart);
+    if (n >= kWideRows)
+      hipLaunchKernelGGL((gemv_n_kernel<T, true>), dim3((unsigned)m), dim3(256), 0, s, Ap, A.ld, A.ps, (int)m, (int)n, v, w);
+    else
+      hipLaunchKernelGGL((gemv_n_kernel<T, false>), dim3((unsigned)((m + 3) / 4)), dim3(256), 0, s, Ap, A.ld, A.ps, (int)m, (int)n,
+                         v, w);
+    // the estimate is wanted after the last two steps only, and no v after the last
+    if (k + 2 >= steps)
+      hipLaunchKernelGGL(sumsq_kernel, dim3(1), dim3(256), 0, s, w, 4 * m, lambda, k + 1 == steps && k > 0 ? lambda + 1 : (double*)nullptr);
+    if (k + 1 == steps) break;
+    if (wide_columns(n, nrb))
+      hipLaunchKernelGGL((gemv_h_kernel<T, 256>), dim3((unsigned)((n + 255) / 256), (unsigned)nrb), dim3(256), 0, s, Ap, A.ld,
+                         A.ps, (int)m, (int)n, w, zpart);
+    else
+      hipLaunchKernelGGL((gemv_h_kernel<T, 32>), dim3((unsigned)((n + 31) / 32), (unsigned)nrb), dim3(256), 0, s, Ap, A.ld,
+                         A.ps, (int)m, (int)n, w, zpart);
     hipLaunchKernelGGL(sum_parts_kernel, dim3((unsigned)((4 * n + 255) / 256)), dim3(256), 0, s, zpart, nrb, 4 * n, v);
     QP_HIP(hipGetLastError());
   }
+  QP_HIP(hipGetLastError());
   if (steps == 1) hipLaunchKernelGGL(copy1_kernel, dim3(1), dim3(64), 0, s, lambda, lambda + 1);
 }
 
