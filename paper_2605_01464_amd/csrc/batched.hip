@@ -18,7 +18,7 @@
 
 #include "batched.hpp"
 #include "controller.hpp"
-#include "qgemm_kern.hpp"
+#include "qgemm8_kern.hpp"
 
 namespace qp {
 
@@ -118,10 +118,40 @@ __device__ __forceinline__ DEpi epi_out(const DM& o, float a = 1.f, float g = 0.
   return e;
 }
 
+// Products of the 32 x 32 kernels with eight real products per quaternion product (qgemm8_kern.hpp): half the MFMAs of the
+// direct form, which stays where its rounding error is the smaller one (sums of fewer than 16 terms) and where an element's
+// sums with others could leave the type's range.  The choice is the matrix's, so every product of its solve and both kernel
+// forms take the same one.
+template <class MM, int BM, int BN, int WM, int WN>
+struct Eight {
+  static constexpr bool on = false;
+  static constexpr int SMEM = 0;
+};
+template <int WM, int WN>
+struct Eight<MM16F, 32, 32, WM, WN> {
+  static constexpr bool on = true;
+  static constexpr int SMEM = 2 * Gemm8Cfg<MM16F, 32, 32, WM, WN>::STAGE;
+};
+__device__ __forceinline__ bool takes_eight(int m, int n, double normA) {
+  return min(m, n) >= 16 && normA > 1e-12 && normA < 1e12;
+}
+
+// Tile t of a product (the eight-product form takes operands whose rows are 16-byte aligned).
+template <class MM, int BM, int BN, int BK, int WM, int WN, int LOAD, bool OVERLAP>
+__device__ __forceinline__ void batch_tile(const GemmParams<float>& P, int t, bool eight, float* smem, double& a0, double& a1) {
+  if constexpr (Eight<MM, BM, BN, WM, WN>::on) {
+    if (eight) {
+      gemm8_tile<MM, BM, BN, WM, WN, 128>(P, t / P.tiles_n, t % P.tiles_n, smem, a0, a1);
+      return;
+    }
+  }
+  gemm_tile<MM, BM, BN, BK, WM, WN, 128, LOAD, false, OVERLAP>(P, t / P.tiles_n, t % P.tiles_n, smem, a0, a1);
+}
+
 // C = A B with the epilogue, all tiles of the output walked by this workgroup; returns the
 // workgroup totals of the reduction terms in (sd, sx) when e.reduce.
 template <class MM, int BM, int BN, int BK, int WM, int WN>
-__device__ __attribute__((noinline)) void wg_gemm(const DM& A, const DM& B, const DEpi& e, float* smem, double* sh,
+__device__ __attribute__((noinline)) void wg_gemm(const DM& A, const DM& B, const DEpi& e, bool eight, float* smem, double* sh,
                                                   double& sd, double& sx) {
   GemmParams<float> P;
   P.A = A.p;
@@ -154,7 +184,8 @@ __device__ __attribute__((noinline)) void wg_gemm(const DM& A, const DM& B, cons
   P.reduce = e.reduce;
   double a0 = 0.0, a1 = 0.0;
   const int nt = P.tiles_m * P.tiles_n;
-  for (int t = 0; t < nt; ++t) gemm_tile<MM, BM, BN, BK, WM, WN, 128>(P, t / P.tiles_n, t % P.tiles_n, smem, a0, a1);
+  for (int t = 0; t < nt; ++t)
+    batch_tile<MM, BM, BN, BK, WM, WN, kLoadScalar, false>(P, t, eight, smem, a0, a1);
   if (e.reduce) {
     sd = wg_sum(a0, sh);
     sx = wg_sum(a1, sh);
@@ -605,7 +636,8 @@ __device__ __forceinline__ bool setup_matrix(int scaling, int power_steps, unsig
 template <class MM, int BM, int BN, int BK, int WM, int WN>
 __global__ void __launch_bounds__(64 * WM * WN) batched_kernel(BParams P) {
   using C = GemmCfg<MM, BM, BN, BK, WM, WN>;
-  __shared__ __attribute__((aligned(16))) float smem[C::SMEM];
+  constexpr int SMEM = Eight<MM, BM, BN, WM, WN>::SMEM > C::SMEM ? Eight<MM, BM, BN, WM, WN>::SMEM : C::SMEM;
+  __shared__ __attribute__((aligned(16))) float smem[SMEM];
   static_assert(C::SMEM >= 4 * 32 * 33 && C::SMEM >= 2 * 4 * 64 * 4, "set-up scratch fits in the staging LDS");
   __shared__ double sh[16];
   __shared__ int s_next;
@@ -653,14 +685,16 @@ __global__ void __launch_bounds__(64 * WM * WN) batched_kernel(BParams P) {
 
     DM X[4] = {buf(BX, n, m), buf(BX + 1, n, m), buf(BX + 2, n, m), buf(BX + 3, n, m)};
     double normA = 0.0, alpha = 0.0;
-    DM none;
-    none.p = nullptr;
-    if (!setup_matrix(P.scaling, P.power_steps, P.seed, P.scaling == 2 ? P.alpha[b] : 0.0, A, none, X[0], dw, D, sh, smem,
+    DM Ac = buf(BE, m, n);  // the copy of A with 16-byte aligned rows, where the descriptor asks for one (free until the
+    if (d.ldap == 0) Ac.p = nullptr;  // rise rule's candidate products, which end the solve)
+    if (!setup_matrix(P.scaling, P.power_steps, P.seed, P.scaling == 2 ? P.alpha[b] : 0.0, A, Ac, X[0], dw, D, sh, smem,
                       C::SMEM,
                       info, normA, alpha)) {
       if (tid == 0) P.info[b] = info;
       continue;
     }
+    if (Ac.p != nullptr) A = Ac;
+    const bool eight = takes_eight(m, n, normA);
 
     // ---------------------------------------------------------------- iterations
     StopController ctl(P.stop, P.tol);
@@ -685,9 +719,9 @@ __global__ void __launch_bounds__(64 * WM * WN) batched_kernel(BParams P) {
       auto prod = [&](const DEpi& e) {
         double t0, t1;
         if (left)
-          wg_gemm<MM, BM, BN, BK, WM, WN>(Xc, A, e, smem, sh, t0, t1);
+          wg_gemm<MM, BM, BN, BK, WM, WN>(Xc, A, e, eight, smem, sh, t0, t1);
         else
-          wg_gemm<MM, BM, BN, BK, WM, WN>(A, Xc, e, smem, sh, t0, t1);
+          wg_gemm<MM, BM, BN, BK, WM, WN>(A, Xc, e, eight, smem, sh, t0, t1);
       };
       double sd = 0.0, sx = 0.0;
       auto apply = [&](const DM& T) {
@@ -697,9 +731,9 @@ __global__ void __launch_bounds__(64 * WM * WN) batched_kernel(BParams P) {
         e.ref = 0;
         e.reduce = 1;
         if (left)
-          wg_gemm<MM, BM, BN, BK, WM, WN>(T, Xc, e, smem, sh, sd, sx);
+          wg_gemm<MM, BM, BN, BK, WM, WN>(T, Xc, e, eight, smem, sh, sd, sx);
         else
-          wg_gemm<MM, BM, BN, BK, WM, WN>(Xc, T, e, smem, sh, sd, sx);
+          wg_gemm<MM, BM, BN, BK, WM, WN>(Xc, T, e, eight, smem, sh, sd, sx);
       };
       const DM R = buf(0, s, s);
       double t0, t1;
@@ -720,7 +754,7 @@ __global__ void __launch_bounds__(64 * WM * WN) batched_kernel(BParams P) {
         e.a[1] = -1.f;
         e.g[1] = 2.f;
         prod(e);
-        wg_gemm<MM, BM, BN, BK, WM, WN>(R, R, epi_out(R2), smem, sh, t0, t1);
+        wg_gemm<MM, BM, BN, BK, WM, WN>(R, R, epi_out(R2), eight, smem, sh, t0, t1);
         DEpi e4;
         e4.nout = 2;
         e4.out[0] = P1;
@@ -730,9 +764,9 @@ __global__ void __launch_bounds__(64 * WM * WN) batched_kernel(BParams P) {
         e4.b[0][0] = P.k.beta1;
         e4.b[1][0] = P.k.beta2;
         e4.g[0] = e4.g[1] = 1.f;
-        wg_gemm<MM, BM, BN, BK, WM, WN>(R2, R2, e4, smem, sh, t0, t1);
-        wg_gemm<MM, BM, BN, BK, WM, WN>(P1, P2, epi_out(Qm), smem, sh, t0, t1);
-        wg_gemm<MM, BM, BN, BK, WM, WN>(Sp, Qm, epi_out(R2), smem, sh, t0, t1);
+        wg_gemm<MM, BM, BN, BK, WM, WN>(R2, R2, e4, eight, smem, sh, t0, t1);
+        wg_gemm<MM, BM, BN, BK, WM, WN>(P1, P2, epi_out(Qm), eight, smem, sh, t0, t1);
+        wg_gemm<MM, BM, BN, BK, WM, WN>(Sp, Qm, epi_out(R2), eight, smem, sh, t0, t1);
         apply(R2);
       } else {  // QHPI19 (Algorithm 3)
         const DM R2 = buf(1, s, s), R4 = buf(2, s, s), S = buf(3, s, s), P1 = buf(4, s, s), P2 = buf(5, s, s),
@@ -745,7 +779,7 @@ __global__ void __launch_bounds__(64 * WM * WN) batched_kernel(BParams P) {
           e.nin = 1;
           e.in[0] = R;
           e.b[1][0] = 1.f;
-          wg_gemm<MM, BM, BN, BK, WM, WN>(R, R, e, smem, sh, t0, t1);
+          wg_gemm<MM, BM, BN, BK, WM, WN>(R, R, e, eight, smem, sh, t0, t1);
         }
         {
           DEpi e = epi_out(R4);
@@ -757,7 +791,7 @@ __global__ void __launch_bounds__(64 * WM * WN) batched_kernel(BParams P) {
           e.b[1][0] = P.k.d1;
           e.b[2][0] = P.k.d2;
           e.g[1] = e.g[2] = 1.f;
-          wg_gemm<MM, BM, BN, BK, WM, WN>(R2, R2, e, smem, sh, t0, t1);
+          wg_gemm<MM, BM, BN, BK, WM, WN>(R2, R2, e, eight, smem, sh, t0, t1);
         }
         {
           DEpi e;
@@ -770,7 +804,7 @@ __global__ void __launch_bounds__(64 * WM * WN) batched_kernel(BParams P) {
           e.b[0][0] = P.k.d3;
           e.b[1][0] = P.k.e1;
           e.b[1][1] = P.k.e2;
-          wg_gemm<MM, BM, BN, BK, WM, WN>(P1, P2, e, smem, sh, t0, t1);
+          wg_gemm<MM, BM, BN, BK, WM, WN>(P1, P2, e, eight, smem, sh, t0, t1);
         }
         {
           DEpi e = epi_out(P1);
@@ -779,9 +813,9 @@ __global__ void __launch_bounds__(64 * WM * WN) batched_kernel(BParams P) {
           e.in[1] = R4;
           e.b[0][0] = P.k.c1;
           e.b[0][1] = P.k.c2;
-          wg_gemm<MM, BM, BN, BK, WM, WN>(V, Wm, e, smem, sh, t0, t1);
+          wg_gemm<MM, BM, BN, BK, WM, WN>(V, Wm, e, eight, smem, sh, t0, t1);
         }
-        wg_gemm<MM, BM, BN, BK, WM, WN>(S, P1, epi_out(P2, 1.f, 1.f), smem, sh, t0, t1);
+        wg_gemm<MM, BM, BN, BK, WM, WN>(S, P1, epi_out(P2, 1.f, 1.f), eight, smem, sh, t0, t1);
         apply(P2);
       }
       // keep R_{j-1} (residual of X_{j-1}) for the candidate choice of the guarded rule
@@ -833,14 +867,14 @@ __global__ void __launch_bounds__(64 * WM * WN) batched_kernel(BParams P) {
           e.reduce = 1;
           double q0, q1;
           if (left)
-            wg_gemm<MM, BM, BN, BK, WM, WN>(Ra, X[best0], e, smem, sh, q0, q1);
+            wg_gemm<MM, BM, BN, BK, WM, WN>(Ra, X[best0], e, eight, smem, sh, q0, q1);
           else
-            wg_gemm<MM, BM, BN, BK, WM, WN>(X[best0], Ra, e, smem, sh, q0, q1);
+            wg_gemm<MM, BM, BN, BK, WM, WN>(X[best0], Ra, e, eight, smem, sh, q0, q1);
           ea = sqrt(q0) / fmax(xn_hist_a, 1e-300);
           if (left)
-            wg_gemm<MM, BM, BN, BK, WM, WN>(Rb, X[best1], e, smem, sh, q0, q1);
+            wg_gemm<MM, BM, BN, BK, WM, WN>(Rb, X[best1], e, eight, smem, sh, q0, q1);
           else
-            wg_gemm<MM, BM, BN, BK, WM, WN>(X[best1], Rb, e, smem, sh, q0, q1);
+            wg_gemm<MM, BM, BN, BK, WM, WN>(X[best1], Rb, e, eight, smem, sh, q0, q1);
           eb = sqrt(q0) / fmax(xn_hist_b, 1e-300);
         }
         if (ka >= 1 && ea < eb) {
@@ -1219,16 +1253,6 @@ __device__ __forceinline__ GemmParams<float> gemm_params(const DM& Aop, const DM
   return G;
 }
 
-// Tile t of a product: 16-byte operand loads, edge tiles included, when both operands allow them (the
-// work buffers always do; the caller's A only with a 16-byte multiple row stride), else element loads.
-template <class MM, int BM, int BN, int BK, int WM, int WN>
-__device__ __forceinline__ void tile_any(const GemmParams<float>& G, int t, float* smem, double& a0, double& a1) {
-  if (G.vec)
-    gemm_tile<MM, BM, BN, BK, WM, WN, 128, kLoadVec, false, true>(G, t / G.tiles_n, t % G.tiles_n, smem, a0, a1);
-  else
-    gemm_tile<MM, BM, BN, BK, WM, WN, 128, kLoadScalar, false, true>(G, t / G.tiles_n, t % G.tiles_n, smem, a0, a1);
-}
-
 template <int BM, int BN>
 __device__ __forceinline__ int tiles_of(int rows, int cols) {
   return ((rows + BM - 1) / BM) * ((cols + BN - 1) / BN);
@@ -1268,11 +1292,12 @@ constexpr int FLOW_ITEMS = 6;
 template <class MM, int BM, int BN, int BK, int WM, int WN, int PER_CU = 2, bool FLOW = false>
 __global__ void __launch_bounds__(64 * WM * WN, PER_CU) batched_sync_kernel(SParams P) {
   using C = GemmCfg<MM, BM, BN, BK, WM, WN>;
-  __shared__ __attribute__((aligned(16))) float smem[C::SMEM];
+  constexpr int SMEM = Eight<MM, BM, BN, WM, WN>::SMEM > C::SMEM ? Eight<MM, BM, BN, WM, WN>::SMEM : C::SMEM;
+  __shared__ __attribute__((aligned(16))) float smem[SMEM];
   static_assert(C::SMEM >= 4 * 32 * 33 && C::SMEM >= 2 * 4 * 64 * 4, "set-up scratch fits in the staging LDS");
   __shared__ double sh[16];
   __shared__ int pref[SYNC_MAX + 1];
-  __shared__ int s_mn[SYNC_MAX];  // m | n << 16 per matrix
+  __shared__ unsigned short s_tl[SYNC_MAX];  // tiles per matrix, less one: of its s x s products | of its n x m ones << 8
   __shared__ unsigned char s_fl[SYNC_MAX];  // state of each matrix at the start of the update (phase_items)
   __shared__ int s_total;
   __shared__ int s_item;
@@ -1293,7 +1318,10 @@ __global__ void __launch_bounds__(64 * WM * WN, PER_CU) batched_sync_kernel(SPar
   } while (0)
   QP_STAMP();
 
-  for (int b = tid; b < P.count; b += nthr) s_mn[b] = P.desc[b].m | (P.desc[b].n << 16);
+  for (int b = tid; b < P.count; b += nthr) {
+    const int m = P.desc[b].m, n = P.desc[b].n, sd = m > n ? n : m;
+    s_tl[b] = (unsigned short)((tiles_of<BM, BN>(sd, sd) - 1) | (tiles_of<BM, BN>(n, m) - 1) << 8);
+  }
 
   // ---------------------------------------------------------------- set-up: one workgroup per matrix
   for (int b = blockIdx.x; b < P.count; b += G) {
@@ -1370,9 +1398,7 @@ __global__ void __launch_bounds__(64 * WM * WN, PER_CU) batched_sync_kernel(SPar
         const int b = tid * per + q;
         int c = 0;
         if (b < P.count) {
-          const int mb = s_mn[b] & 0xffff, nb = s_mn[b] >> 16;
-          const int sd = mb > nb ? nb : mb;
-          c = phase_items(s_fl[b], ph, np, tiles_of<BM, BN>(sd, sd), tiles_of<BM, BN>(nb, mb));
+          c = phase_items(s_fl[b], ph, np, (s_tl[b] & 0xff) + 1, (s_tl[b] >> 8) + 1);
           pref[b + 1] = c;
         }
         loc += c;
@@ -1514,7 +1540,7 @@ __global__ void __launch_bounds__(64 * WM * WN, PER_CU) batched_sync_kernel(SPar
           GemmParams<float> Gp = left ? gemm_params(Rr, Xr, eo, BM, BN) : gemm_params(Xr, Rr, eo, BM, BN);
           make_uniform(Gp);
           double a0 = 0.0, a1 = 0.0;
-          tile_any<MM, BM, BN, BK, WM, WN>(Gp, t, smem, a0, a1);
+          batch_tile<MM, BM, BN, BK, WM, WN, kLoadVec, true>(Gp, t, uni((int)takes_eight(d.m, d.n, S.normA)) != 0, smem, a0, a1);
           a0 = wg_sum(a0, sh);
           if (tid == 0) P.partial[d.poff + 2 * ((ph - 1) * tiles_of<BM, BN>(d.n, d.m) + t)] = a0;
           __syncthreads();
@@ -1549,7 +1575,7 @@ __global__ void __launch_bounds__(64 * WM * WN, PER_CU) batched_sync_kernel(SPar
           GemmParams<float> Gp = gemm_params(Aop, Bop, e, BM, BN);
           make_uniform(Gp);
           double a0 = 0.0, a1 = 0.0;
-          tile_any<MM, BM, BN, BK, WM, WN>(Gp, t, smem, a0, a1);
+          batch_tile<MM, BM, BN, BK, WM, WN, kLoadVec, true>(Gp, t, uni((int)takes_eight(d.m, d.n, S.normA)) != 0, smem, a0, a1);
           if (ph == np) {
             a0 = wg_sum(a0, sh);
             a1 = wg_sum(a1, sh);
@@ -1770,6 +1796,13 @@ int batched_num_configs() { return (int)batched_table().size(); }
 const char* batched_config_name(int cfg) { return batched_table().at(cfg).name; }
 bool batched_is_sync(int cfg) { return batched_table().at(cfg).sfn != nullptr; }
 
+// The side product takes 16-byte loads of A at 32-bit offsets in a plane: a copy unless the caller's rows and planes allow them.
+static int64_t copied_ld(const BDesc& d) {
+  const bool fits = ((d.lda | d.psa) & 3) == 0 && (reinterpret_cast<uintptr_t>(d.A) & 15) == 0 &&
+                    (d.m + 1) * d.lda < (int64_t(1) << 29);
+  return fits ? 0 : (d.n + 3) / 4 * 4;
+}
+
 void batched_layout(std::vector<BDesc>& desc, int cfg, int64_t& pool, int64_t& part, int64_t& dwork) {
   const auto& ent = batched_table().at(cfg);
   auto up4 = [](int64_t x) { return (x + 3) / 4 * 4; };
@@ -1780,9 +1813,7 @@ void batched_layout(std::vector<BDesc>& desc, int cfg, int64_t& pool, int64_t& p
     d.pss = s * d.lds;
     d.ldw = up4(d.m);
     d.psw = (int64_t)d.n * d.ldw;
-    // the side product takes 16-byte loads of A: a copy unless its rows and planes are 16-byte aligned
-    const bool aligned = ((d.lda | d.psa) & 3) == 0 && (reinterpret_cast<uintptr_t>(d.A) & 15) == 0;
-    d.ldap = aligned ? 0 : up4(d.n);
+    d.ldap = copied_ld(d);
     d.psap = (int64_t)d.m * d.ldap;
     d.off = pool;
     pool += 4 * (10 * d.pss + 5 * d.psw + d.psap);
@@ -1986,8 +2017,9 @@ void run_batched(BatchedState& st, const BKey& key, const std::vector<BDesc>& de
     batched_layout(desc, key.cfg, pool, part, dw);
     if (!st.exec || !(st.key == key) || pool > st.pool_cap || part > st.part_cap || dw > st.dw_cap)
       build_sync(st, key, pool + pool / 4 + 64, part + part / 4 + 64, dw + dw / 4 + 64);
-  } else if (!st.exec || !(st.key == key) || st.pool_cap != 0) {
-    build(st, key, caller);
+  } else {
+    for (BDesc& d : desc) d.ldap = copied_ld(d);
+    if (!st.exec || !(st.key == key) || st.pool_cap != 0) build(st, key, caller);
   }
   std::memcpy(st.h_desc, desc.data(), sizeof(BDesc) * count);
   if (!sync) std::memcpy(st.h_order, order.data(), sizeof(int) * count);
