@@ -141,7 +141,7 @@ template <class MM, int BM, int BN, int BK, int WM, int WN, int LOAD, bool OVERL
 __device__ __forceinline__ void batch_tile(const GemmParams<float>& P, int t, bool eight, float* smem, double& a0, double& a1) {
   if constexpr (Eight<MM, BM, BN, WM, WN>::on) {
     if (eight) {
-      gemm8_tile<MM, BM, BN, WM, WN, 128>(P, t / P.tiles_n, t % P.tiles_n, smem, a0, a1);
+      gemm8_tile<MM, BM, BN, WM, WN, 2, 128>(P, t / P.tiles_n, t % P.tiles_n, smem, a0, a1);
       return;
     }
   }

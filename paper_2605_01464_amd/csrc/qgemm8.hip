@@ -6,7 +6,7 @@
 
 namespace qp {
 
-template <class MM, int BM, int BN, int WM, int WN, int FLUSH, int MINW>
+template <class MM, int BM, int BN, int WM, int WN, int PF, int FLUSH, int MINW>
 __global__ void __launch_bounds__(64 * WM * WN, MINW) qgemm8_kernel(GemmParams<typename MM::T> P) {
   using C = Gemm8Cfg<MM, BM, BN, WM, WN>;
   __shared__ __attribute__((aligned(16))) typename MM::T smem[2 * C::STAGE];
@@ -14,7 +14,7 @@ __global__ void __launch_bounds__(64 * WM * WN, MINW) qgemm8_kernel(GemmParams<t
   double s_d = 0.0, s_x = 0.0;
   int tm, tn;
   tile_of_block(blockIdx.x, P.tiles_m * P.tiles_n, P.tiles_m, P.tiles_n, tm, tn);
-  gemm8_tile<MM, BM, BN, WM, WN, FLUSH>(P, tm, tn, smem, s_d, s_x);
+  gemm8_tile<MM, BM, BN, WM, WN, PF, FLUSH>(P, tm, tn, smem, s_d, s_x);
   store_partials<C::NW>(P.partial, s_d, s_x, red_lds, threadIdx.x & 63, threadIdx.x >> 6, threadIdx.x);
 }
 
@@ -29,7 +29,7 @@ __global__ void __launch_bounds__(64 * NWV, MINW) qgemm8_regs_kernel(GemmParams<
   store_partials<NWV>(P.partial, s_d, s_x, red_lds, threadIdx.x & 63, threadIdx.x >> 6, threadIdx.x);
 }
 
-template <class MM, int BM, int BN, int WM, int WN, int FLUSH, int MINW>
+template <class MM, int BM, int BN, int WM, int WN, int PF, int FLUSH, int MINW>
 static int64_t launch8(const GemmParams<typename MM::T>& P0, hipStream_t s) {
   using C = Gemm8Cfg<MM, BM, BN, WM, WN>;
   GemmParams<typename MM::T> P = P0;
@@ -37,7 +37,7 @@ static int64_t launch8(const GemmParams<typename MM::T>& P0, hipStream_t s) {
   P.tiles_n = (P.N + BN - 1) / BN;
   const int64_t nt = (int64_t)P.tiles_m * P.tiles_n;
   if (nt == 0) return 0;
-  hipLaunchKernelGGL((qgemm8_kernel<MM, BM, BN, WM, WN, FLUSH, MINW>), dim3((unsigned)nt), dim3(C::NT), 0, s, P);
+  hipLaunchKernelGGL((qgemm8_kernel<MM, BM, BN, WM, WN, PF, FLUSH, MINW>), dim3((unsigned)nt), dim3(C::NT), 0, s, P);
   QP_HIP(hipGetLastError());
   return nt;
 }
@@ -64,8 +64,8 @@ struct Entry8 {
 // 16 x 16 in registers (4 waves, each every fourth block of k; three workgroups per unit in FP64, four in FP32).
 static const std::vector<Entry8<double>>& f64_table8() {
   static const std::vector<Entry8<double>> t = {
-      {{0, 64, 64, 8, 512, "f64x8_64x64_w2x4"}, launch8<MM16D, 64, 64, 2, 4, 0, 2>},
-      {{1, 32, 32, 8, 256, "f64x8_32x32_w2x2"}, launch8<MM16D, 32, 32, 2, 2, 0, 2>},
+      {{0, 64, 64, 8, 512, "f64x8_64x64_w2x4"}, launch8<MM16D, 64, 64, 2, 4, 2, 0, 2>},
+      {{1, 32, 32, 8, 256, "f64x8_32x32_w2x2"}, launch8<MM16D, 32, 32, 2, 2, 2, 0, 2>},
       {{2, 16, 16, 8, 256, "f64x8_16x16_regs4"}, launch8_regs<MM16D, 1, 1, 4, 1, 3>},
   };
   return t;
@@ -75,8 +75,8 @@ static const std::vector<Entry8<double>>& f64_table8() {
 // quarter of k, which kRegsMaxK keeps at 512, the 128 dependent MFMAs that the direct form's 128 k take.
 static const std::vector<Entry8<float>>& f32_table8() {
   static const std::vector<Entry8<float>> t = {
-      {{0, 64, 64, 16, 1024, "f32x8_64x64_w4x4"}, launch8<MM16F, 64, 64, 4, 4, 128, 4>},
-      {{1, 32, 32, 16, 256, "f32x8_32x32_w2x2"}, launch8<MM16F, 32, 32, 2, 2, 128, 2>},
+      {{0, 64, 64, 16, 1024, "f32x8_64x64_w4x4"}, launch8<MM16F, 64, 64, 4, 4, 1, 128, 4>},
+      {{1, 32, 32, 16, 256, "f32x8_32x32_w2x2"}, launch8<MM16F, 32, 32, 2, 2, 2, 128, 2>},
       {{2, 16, 16, 16, 256, "f32x8_16x16_regs4"}, launch8_regs<MM16F, 1, 1, 4, 1, 4>},
   };
   return t;
@@ -95,19 +95,19 @@ const std::vector<TileConfig>& eight_configs(Prec p) {
 
 // The tile that takes the least time by a model of rounds: with `cap` workgroups resident on the chip, every full round costs
 // full x K microseconds and the last, partial one `part` x K if it leaves at most one workgroup per unit.  Measured, FP64 (us):
-//   K = 300, 300 x 300:    64 x 64 91    32 x 32 36    16 x 16 19     (direct form 55)
-//   K = 1000, 500 x 500:   64 x 64 268   32 x 32 107   16 x 16 95     (170)
-//   K = 700, 700 x 700:    64 x 64 197   32 x 32 131   16 x 16 142    (204)
-//   K = 1000, 1000 x 1000: 64 x 64 304   32 x 32 364   16 x 16 415    (564)
-//   K = 4096, 4096 x 4096: 64 x 64 17089 32 x 32 20071                (30600; 64.3 TFLOP/s of MFMA work)
-// and FP32: 300^3 49 / 23 / 12 (41), 700^3 107 / 74 / 76 (138), 1000^3 163 / 200 / 251 (326), 4096^3 8863 / 10760 (15931).
+//   K = 300, 300 x 300:    64 x 64 90    32 x 32 34    16 x 16 19     (direct form 55)
+//   K = 1000, 500 x 500:   64 x 64 267   32 x 32 100   16 x 16 94     (170)
+//   K = 700, 700 x 700:    64 x 64 197   32 x 32 128   16 x 16 142    (208)
+//   K = 1000, 1000 x 1000: 64 x 64 300   32 x 32 346   16 x 16 377    (565)
+//   K = 4096, 4096 x 4096: 64 x 64 16830 32 x 32 19400                (30600; 65.3 TFLOP/s of MFMA work)
+// and FP32: 300^3 48 / 22 / 12 (41), 700^3 107 / 72 / 76 (138), 1000^3 162 / 195 / 234 (320), 4096^3 8720 / 10320 (15920).
 int eight_default(Prec p, int64_t M, int64_t N, int64_t K) {
   struct Cost {
     int64_t tile, cap;
     double full, part, fixed;
   };
-  static constexpr Cost k64[3] = {{64, 256, 0.27, 0.27, 12}, {32, 512, 0.175, 0.1, 6}, {16, 512, 0.05, 0.025, 3}};
-  static constexpr Cost k32[3] = {{64, 256, 0.14, 0.14, 10}, {32, 512, 0.1, 0.062, 5}, {16, 768, 0.041, 0.017, 3}};
+  static constexpr Cost k64[3] = {{64, 256, 0.27, 0.27, 12}, {32, 512, 0.17, 0.094, 6}, {16, 512, 0.046, 0.025, 3}};
+  static constexpr Cost k32[3] = {{64, 256, 0.14, 0.14, 10}, {32, 512, 0.095, 0.057, 5}, {16, 768, 0.041, 0.017, 3}};
   int best = 0;
   double best_t = 0.0;
   for (int i = 0; i < 3; ++i) {

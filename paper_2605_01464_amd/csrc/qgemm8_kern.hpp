@@ -47,8 +47,11 @@ __device__ __forceinline__ void planes_of(const T (&P)[8], T (&c)[4]) {
 //
 // The K loop is one software pipeline over the products t of the steps s: the fragments of product t + PD are read behind the
 // MFMAs of product t; the sums of step s + 1 are written to the other stage behind products 1..4 of step s, after which the
-// loads of step s + 2 go out; the one barrier of a step stands before the first read from the new stage, PD products before
-// the step's end.
+// loads of step s + 1 + PF go out; the one barrier of a step stands before the first read from the new stage, PD products
+// before the step's end.  PF = 2 holds two steps of loads in registers: the loads behind products 5..7 alone hide about 400
+// cycles, less than one takes.  Where the registers have room for it (all but the 16-wave FP32 tile, at 115 of 128): 32 x 32
+// tiles at 4096^3 FP64 20.15 -> 19.3 ms, FP32 10.77 -> 10.32; 500 x 500 x 1000 108 -> 100 and 64.6 -> 61.4 us; 64 x 64 FP64 at
+// 4096^3 16.98 -> 16.83 ms.
 // ------------------------------------------------------------------------------------------------
 template <class MM, int BM, int BN, int WM, int WN>
 struct Gemm8Cfg {
@@ -66,7 +69,7 @@ struct Gemm8Cfg {
   static_assert(ACH % 64 == 0 && (BN & (BN - 1)) == 0, "chunks");
 };
 
-template <class MM, int BM, int BN, int WM, int WN, int FLUSH>
+template <class MM, int BM, int BN, int WM, int WN, int PF, int FLUSH>
 __device__ __forceinline__ void gemm8_tile(const GemmParams<typename MM::T>& P, int tm, int tn, typename MM::T* smem,
                                            double& s_d, double& s_x) {
   using C = Gemm8Cfg<MM, BM, BN, WM, WN>;
@@ -74,6 +77,7 @@ __device__ __forceinline__ void gemm8_tile(const GemmParams<typename MM::T>& P, 
   using Acc = typename MM::Acc;
   using VG = typename V16<T>::nat;
   constexpr int VA = C::VA, BK = C::BK, NC = C::NC, NB = 4, PD = 2;
+  static_assert(PF == 1 || PF == 2, "steps in flight");
   static_assert(FLUSH % BK == 0, "flush interval is a whole number of steps");
   const int m0 = tm * BM, n0 = tn * BN;
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -104,8 +108,8 @@ __device__ __forceinline__ void gemm8_tile(const GemmParams<typename MM::T>& P, 
       dst[u] = BM * BK + k * BN + (jc ^ (k / VA % C::FLIPS * C::FLIP)) * VA;
     }
   }
-  VG g[NC][4];
-  auto load = [&](int s) __attribute__((always_inline)) {
+  VG gs[PF][NC][4];  // the steps in flight (`load`, `mask` and `put` take the step's slot)
+  auto load = [&](int s, int d) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < NC; ++u) {
       if (!active(u)) continue;
@@ -121,12 +125,12 @@ __device__ __forceinline__ void gemm8_tile(const GemmParams<typename MM::T>& P, 
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const char* const pl = reinterpret_cast<const char*>(base + (a ? q : b_plane(q)) * ps);
-        g[u][q] = gload(reinterpret_cast<const VG*>(pl + (uint32_t)(v * (unsigned)sizeof(T))), 0);
+        gs[d][u][q] = gload(reinterpret_cast<const VG*>(pl + (uint32_t)(v * (unsigned)sizeof(T))), 0);
       }
     }
   };
   // elements of step s whose k lies outside the matrix become zeros
-  auto mask = [&](int s) __attribute__((always_inline)) {
+  auto mask = [&](int s, int d) __attribute__((always_inline)) {
     if ((s + 1) * BK <= P.K) return;
 #pragma unroll
     for (int u = 0; u < NC; ++u)
@@ -134,19 +138,20 @@ __device__ __forceinline__ void gemm8_tile(const GemmParams<typename MM::T>& P, 
       for (int e = 0; e < VA; ++e) {
         const bool in = s * BK + kk[u] + (is_a(u) ? e : 0) < P.K;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) g[u][q][e] = in ? g[u][q][e] : T(0);
+        for (int q = 0; q < 4; ++q) gs[d][u][q][e] = in ? gs[d][u][q][e] : T(0);
       }
   };
   // sums t and t + 1 of the loaded step
-  auto put = [&](T* st, int t) __attribute__((always_inline)) {
+  auto put = [&](T* st, int t, int d) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < NC; ++u) {
       if (!active(u)) continue;
+      const VG(&g)[4] = gs[d][u];
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         VG v;
 #pragma unroll
-        for (int e = 0; e < VA; ++e) v[e] = sum8(t + h, g[u][0][e], g[u][1][e], g[u][2][e], g[u][3][e]);
+        for (int e = 0; e < VA; ++e) v[e] = sum8(t + h, g[0][e], g[1][e], g[2][e], g[3][e]);
         *reinterpret_cast<VG*>(st + dst[u] + (t + h) * C::SUM) = v;
       }
     }
@@ -217,19 +222,20 @@ __device__ __forceinline__ void gemm8_tile(const GemmParams<typename MM::T>& P, 
 
   __syncthreads();  // the caller may have used the LDS just before
   if (ns > 0) {
-    load(0);
-    mask(0);
+    load(0, 0);
+    mask(0, 0);
 #pragma unroll
-    for (int t = 0; t < 8; t += 2) put(smem, t);
-    load(ns > 1 ? 1 : 0);
+    for (int t = 0; t < 8; t += 2) put(smem, t, 0);
+#pragma unroll
+    for (int d = 1; d <= PF; ++d) load(d, d % PF);
     __syncthreads();
 #pragma unroll
     for (int t = 0; t < PD; ++t) read(smem, t);
   }
-  for (int s = 0; s < ns; ++s) {
-    T* const st = smem + (s & 1) * C::STAGE;
-    T* const nx = smem + ((s & 1) ^ 1) * C::STAGE;
-    const bool more = s + 1 < ns;
+  auto step = [&](int s, int h) __attribute__((always_inline)) {  // h: the step's stage
+    T* const st = smem + h * C::STAGE;
+    T* const nx = smem + (h ^ 1) * C::STAGE;
+    const int d = (h + 1) % PF;  // the slot of step s + 1
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
       if (t == 8 - PD) {
@@ -240,9 +246,9 @@ __device__ __forceinline__ void gemm8_tile(const GemmParams<typename MM::T>& P, 
         asm volatile("" ::: "memory");
       }
       read(t + PD < 8 ? st : nx, (t + PD) % 8);
-      if (t == 0) mask(s + 1);
-      if (t >= 1 && t <= 4) put(nx, 2 * (t - 1));
-      if (t == 5) load(s + 2);
+      if (t == 0) mask(s + 1, d);
+      if (t >= 1 && t <= 4) put(nx, 2 * (t - 1), d);
+      if (t == 5) load(s + 1 + PF, d);
 #pragma unroll
       for (int e = 0; e < VA; ++e)
 #pragma unroll
@@ -253,6 +259,14 @@ __device__ __forceinline__ void gemm8_tile(const GemmParams<typename MM::T>& P, 
     }
     if constexpr (FLUSH > 0) {
       if (((s + 1) * BK) % FLUSH == 0 || s + 1 == ns) flush();
+    }
+  };
+  if constexpr (PF == 1) {
+    for (int s = 0; s < ns; ++s) step(s, s & 1);
+  } else {  // the slots need a fixed stage per copy of the step
+    for (int s = 0; s < ns; s += 2) {
+      step(s, 0);
+      if (s + 1 < ns) step(s + 1, 1);
     }
   }
 
