@@ -57,7 +57,6 @@ __global__ void __launch_bounds__(64 * WM * WN, MINW) qgemm_kernel(GemmParams<ty
 template <class MM, int FLUSH, int PF>
 __global__ void __launch_bounds__(256, 1) qgemm_narrow_kernel(GemmParams<typename MM::T> P) {
   using T = typename MM::T;
-  using VG = typename VU<T>::type;
   constexpr int VA = V16<T>::n, KB = VA * MM::KS;
   static_assert(MM::BLK == 16 && MM::NR == 4 && FLUSH % KB == 0, "16 x 16 MFMA");
   __shared__ double red_lds[4][2];
@@ -223,7 +222,10 @@ static KernelLimits kernel_limits(K kern, int threads) {
 }
 
 // Launches the configuration; returns the number of workgroups (partial sums) launched.  PER_CU as
-// TileConfig::per_cu.  The operand load mode is the most specific one the shape and the views allow.
+// TileConfig::per_cu.  The operand load mode is the fastest one that the shape and the views allow: kLoadElems takes any
+// product that is not of whole, aligned tiles, but for offsets beyond 32 bits and the FP64 tiles that have fewer elements
+// than threads (FP32, 1345 x 777 x 1001: 343 us against 533 with kLoadScalar; 1344 x 776 x 1000: 340 against 393 with
+// kLoadVec, whose chunks are masked one by one; 513 x 511 x 509: 79 against 112; FP64 gains 2-8 %).
 // MINW: waves per SIMD the register allocation must leave room for (launch bound).
 template <class MM, int BM, int BN, int BK, int WM, int WN, int FLUSH, bool DB, int MINW, bool WALK, int LM>
 static void launch_mode(const GemmParams<typename MM::T>& P, int64_t grid, size_t dyn_lds, hipStream_t s) {
@@ -234,8 +236,12 @@ static void launch_mode(const GemmParams<typename MM::T>& P, int64_t grid, size_
 
 template <class MM, int BM, int BN, int BK, int WM, int WN, int FLUSH, bool DB, int MINW, bool WALK>
 static void launch_any_mode(const GemmParams<typename MM::T>& P, int64_t grid, size_t dyn_lds, hipStream_t s) {
+  using C = GemmCfg<MM, BM, BN, BK, WM, WN>;
+  constexpr bool ELEMS = BM * BK % C::NT == 0 && BK * BN % C::NT == 0;
   if (P.vec && P.M % BM == 0 && P.N % BN == 0 && P.K % BK == 0)
     launch_mode<MM, BM, BN, BK, WM, WN, FLUSH, DB, MINW, WALK, kLoadAligned>(P, grid, dyn_lds, s);
+  else if (ELEMS && P.M * P.lda < (int64_t(1) << 28) && BK * P.ldb < (int64_t(1) << 28))
+    launch_mode<MM, BM, BN, BK, WM, WN, FLUSH, DB, MINW, WALK, ELEMS ? kLoadElems : kLoadScalar>(P, grid, dyn_lds, s);
   else if (P.vec)
     launch_mode<MM, BM, BN, BK, WM, WN, FLUSH, DB, MINW, WALK, kLoadVec>(P, grid, dyn_lds, s);
   else
@@ -337,15 +343,19 @@ int64_t qgemm_blocks(Prec p, int cfg, int64_t M, int64_t N) {
 // double-buffered tiles (8 waves of 32 x 32, twice the MFMA work per K-step barrier) beat 64 x 64 there
 // (4096^3: 30.8 vs 31.3 ms; 128 x 64 with the same waves 36.6 ms).  BF16 from 1024 tiles
 // of 64 x 64: the staged form with its operand tiles loaded straight into LDS; split BF16: 128 x 128 tiles
-// from 256 of them (one workgroup of 16 waves per CU), 64 x 64 below.
+// from 256 of them (one workgroup of 16 waves per CU), 64 x 64 below.  FP32 and FP64 products of other sizes than whole
+// tiles load element by element, and there the 32 x 32 tiles win at every size: they keep two workgroups per unit and
+// waste less at the edges (FP32 2049 x 2047 x 2045: 2.23 ms against 2.67, 4097^3: 16.8 against 17.4; FP64 4.45 against
+// 6.06, and 33.6 against 35.2).
 int default_config(Prec p, int64_t M, int64_t N, int64_t K) {
   if (p == P_F64E || p == P_F32E) return eight_default(p, M, N, K);
   const int64_t b64 = ((M + 63) / 64) * ((N + 63) / 64);
-  if (p == P_F64) return N <= 16 ? kNarrowConfig : b64 >= 1024 ? 6 : 1;
+  const bool whole = M % 64 == 0 && N % (p == P_F64 ? 128 : 64) == 0 && K % 16 == 0;
+  if (p == P_F64) return N <= 16 ? kNarrowConfig : b64 >= 1024 && whole ? 6 : 1;
   if (p == P_BF16) return b64 >= 1024 ? 11 : b64 >= 256 ? 0 : 1;
   if (p == P_BF16X3) return ((M + 127) / 128) * ((N + 127) / 128) >= 256 ? 4 : 3;
   if (N <= 16) return kNarrowConfig;
-  return b64 >= 1024 ? 5 : 6;
+  return b64 >= 1024 && whole ? 5 : 6;
 }
 
 template <class T>

@@ -314,7 +314,7 @@ __device__ __forceinline__ void gemm8_regs_tile(const GemmParams<typename MM::T>
                                                 double& s_d, double& s_x) {
   using T = typename MM::T;
   using Acc = typename MM::Acc;
-  using VG = typename VU<T>::type;
+  using VG = typename V16<T>::nat;
   constexpr int VA = V16<T>::n, KB = VA * MM::KS, BM = 16 * TM, BN = 16 * TN;
   static_assert(MM::BLK == 16 && MM::NR == 4, "16 x 16 MFMA");
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);

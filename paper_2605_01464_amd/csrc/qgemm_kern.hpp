@@ -61,18 +61,6 @@ struct V16<double> {
   static constexpr int n = 2;
 };
 
-// Sixteen bytes at an address aligned to the element only (global loads take any such address).
-template <class T>
-struct VU;
-template <>
-struct VU<float> {
-  typedef float type __attribute__((ext_vector_type(4), aligned(4)));
-};
-template <>
-struct VU<double> {
-  typedef double type __attribute__((ext_vector_type(2), aligned(8)));
-};
-
 template <class T>
 struct GemmParams {
   const T* A;
@@ -266,7 +254,11 @@ struct GemmCfg {
 //                 read up to ld (never past it), and the elements outside the matrix are replaced by
 //                 zeros: any value there, NaN included, leaves the product unchanged.
 //   kLoadAligned: kLoadVec, and M % BM = N % BN = K % BK = 0: no clamps and no masks.
-enum : int { kLoadScalar = 0, kLoadVec = 1, kLoadAligned = 2 };
+//   kLoadElems:   any ld, lane offsets within a plane that fit 32 bits: consecutive lanes load consecutive elements, from a
+//                 uniform base and an offset that only the last K step changes.  kLoadScalar's lanes each take the four
+//                 elements of a 16-byte chunk one by one, so an instruction touches four times the cache lines, and their
+//                 64-bit addresses are formed anew for every element.
+enum : int { kLoadScalar = 0, kLoadVec = 1, kLoadAligned = 2, kLoadElems = 3 };
 
 // One BM x BN output tile (all four planes) of C = A B with the epilogue; the epilogue's reduction
 // terms are added to the caller's s_d, s_x.  Used by the standalone product kernel and by the batched
@@ -333,19 +325,90 @@ __device__ __forceinline__ void gemm_tile(const GemmParams<typename MM::T>& P, i
     }
   };
 
+  constexpr bool ALIGNED = LM == kLoadAligned, ELEMS = LM == kLoadElems;
   T ra[4][C::NA][VA];
   T rb[4][C::NB][VA];
+  // kLoadElems: a thread's elements of a step (row and k of A, row and column of B), their offsets in step 0 and in LDS.
+  // Rows of A and columns of B outside the matrix are loaded from clamped addresses (what they give only reaches outputs
+  // that are not written).
+  constexpr int EA = ELEMS ? BM * BK / C::NT : 1, EB = ELEMS ? BK * BN / C::NT : 1;
+  static_assert(!ELEMS || (EA * C::NT == BM * BK && EB * C::NT == BK * BN), "whole elements per thread");
+  T xa[4][EA], xb[4][EB];
+  unsigned oa[EA], ob[EB];
+  int ka[EA], kb_[EB], da[EA], db[EB];
+  if constexpr (ELEMS) {
+#pragma unroll
+    for (int u = 0; u < EA; ++u) {
+      const int c = tid + u * C::NT, i = c / BK, k = c % BK;
+      ka[u] = k;
+      oa[u] = (unsigned)min(m0 + i, P.M - 1) * (unsigned)P.lda + k;
+      da[u] = ((k / VA) * C::LDAC + i) * VA + k % VA;
+    }
+#pragma unroll
+    for (int u = 0; u < EB; ++u) {
+      const int c = tid + u * C::NT, k = c / BN, j = c % BN;
+      kb_[u] = k;
+      ob[u] = (unsigned)k * (unsigned)P.ldb + min(n0 + j, P.N - 1);
+      db[u] = k * C::LDB + j;
+    }
+  }
 
   // Edge tiles in kLoadScalar mode load every element from an address clamped into the matrix; in
   // kLoadVec mode the 16-byte chunk is clamped.  Either way the elements outside the matrix are zeroed
   // only when the registers go to LDS, so the loads stay in flight behind the MFMAs like full-tile ones.
-  constexpr bool ALIGNED = LM == kLoadAligned;
   auto full_a = [&](int k0) { return ALIGNED || (LM == kLoadVec && (m0 + BM <= P.M) && (k0 + BK <= P.K)); };
   auto full_b = [&](int k0) { return ALIGNED || (LM == kLoadVec && (n0 + BN <= P.N) && (k0 + BK <= P.K)); };
   using VG = typename V16<T>::nat;
   // last chunk start that holds an element of the matrix (kLoadVec): k chunks of A, column chunks of B
   const int kc_last = ((P.K - 1) / VA) * VA, jc_last = ((P.N - 1) / VA) * VA;
+  auto load_elems = [&](int k0) __attribute__((always_inline)) {
+    unsigned va[EA], vb[EB];
+#pragma unroll
+    for (int u = 0; u < EA; ++u) va[u] = oa[u];
+#pragma unroll
+    for (int u = 0; u < EB; ++u) vb[u] = ob[u];
+    if (k0 + BK > P.K) {  // k beyond the last: the last one (and masked)
+#pragma unroll
+      for (int u = 0; u < EA; ++u) va[u] -= (unsigned)max(k0 + ka[u] - (P.K - 1), 0);
+#pragma unroll
+      for (int u = 0; u < EB; ++u) vb[u] -= (unsigned)max(k0 + kb_[u] - (P.K - 1), 0) * (unsigned)P.ldb;
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const char* const pa = reinterpret_cast<const char*>(P.A + q * P.psa + k0);
+      const char* const pb = reinterpret_cast<const char*>(P.B + q * P.psb + (int64_t)k0 * P.ldb);
+#pragma unroll
+      for (int u = 0; u < EA; ++u)
+        xa[q][u] = gload(reinterpret_cast<const T*>(pa + (uint32_t)(va[u] * (unsigned)sizeof(T))), 0);
+#pragma unroll
+      for (int u = 0; u < EB; ++u)
+        xb[q][u] = gload(reinterpret_cast<const T*>(pb + (uint32_t)(vb[u] * (unsigned)sizeof(T))), 0);
+    }
+  };
+  auto store_elems = [&](T* As, T* Bs, int k0) __attribute__((always_inline)) {
+    if (k0 + BK > P.K) {
+#pragma unroll
+      for (int u = 0; u < EA; ++u)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) xa[q][u] = k0 + ka[u] < P.K ? xa[q][u] : T(0);
+#pragma unroll
+      for (int u = 0; u < EB; ++u)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) xb[q][u] = k0 + kb_[u] < P.K ? xb[q][u] : T(0);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+#pragma unroll
+      for (int u = 0; u < EA; ++u) As[q * (BK / VA) * C::LDAC * VA + da[u]] = xa[q][u];
+#pragma unroll
+      for (int u = 0; u < EB; ++u) Bs[q * BK * C::LDB + db[u]] = xb[q][u];
+    }
+  };
   auto load = [&](int k0) {
+    if constexpr (ELEMS) {
+      load_elems(k0);
+      return;
+    }
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const T* Aq = P.A + q * P.psa;
@@ -393,6 +456,10 @@ __device__ __forceinline__ void gemm_tile(const GemmParams<typename MM::T>& P, i
 
   // registers of K step k0 to LDS
   auto store = [&](T* As, T* Bs, int k0) {
+    if constexpr (ELEMS) {
+      store_elems(As, Bs, k0);
+      return;
+    }
     const bool fullA = full_a(k0), fullB = full_b(k0);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
