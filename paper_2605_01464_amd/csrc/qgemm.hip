@@ -316,6 +316,7 @@ const std::vector<TileConfig>& bf16_configs();    // qgemm_bf16.hip
 const std::vector<TileConfig>& bf16x3_configs();  // qgemm_bf16.hip
 const std::vector<TileConfig>& eight_configs(Prec p);  // qgemm8.hip
 int eight_default(Prec p, int64_t M, int64_t N, int64_t K);
+int64_t eight_blocks(Prec p, int cfg, int64_t M, int64_t N, int64_t K);
 
 const std::vector<TileConfig>& tile_configs(Prec p) {
   static std::vector<TileConfig> f32, f64;
@@ -413,6 +414,7 @@ void qgemm(Prec p, const QView& A, const QView& B, int64_t M, int64_t N, int64_t
   const int64_t nb = narrow          ? (M + 15) / 16
                      : p == P_BF16     ? bf16_blocks(cfg, M, N)
                      : p == P_BF16X3 ? bf16x3_blocks(cfg, M, N)
+                     : p == P_F64E || p == P_F32E ? eight_blocks(p, cfg, M, N, K)
                                      : blocks_for(cfgs[cfg], M, N);
   if (epi.reduce && nb > scratch.capacity / 2) throw Error(-1, "qgemm: reduction scratch too small");
   double* partial = epi.reduce ? scratch.partial : nullptr;

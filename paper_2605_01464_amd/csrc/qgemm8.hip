@@ -14,7 +14,7 @@ __global__ void __launch_bounds__(64 * WM * WN, MINW) qgemm8_kernel(GemmParams<t
   double s_d = 0.0, s_x = 0.0;
   int tm, tn;
   tile_of_block(blockIdx.x, P.tiles_m * P.tiles_n, P.tiles_m, P.tiles_n, tm, tn);
-  gemm8_tile<MM, BM, BN, WM, WN, PF, FLUSH>(P, tm, tn, smem, s_d, s_x);
+  gemm8_tile<MM, BM, BN, WM, WN, PF, FLUSH>(P, P.tm0 + tm, tn, smem, s_d, s_x);
   store_partials<C::NW>(P.partial, s_d, s_x, red_lds, threadIdx.x & 63, threadIdx.x >> 6, threadIdx.x);
 }
 
@@ -25,15 +25,21 @@ __global__ void __launch_bounds__(64 * NWV, MINW) qgemm8_regs_kernel(GemmParams<
   double s_d = 0.0, s_x = 0.0;
   int tm, tn;
   tile_of_block(blockIdx.x, P.tiles_m * P.tiles_n, P.tiles_m, P.tiles_n, tm, tn);
-  gemm8_regs_tile<MM, TM, TN, NWV, PF>(P, tm, tn, smem, s_d, s_x);
+  gemm8_regs_tile<MM, TM, TN, NWV, PF>(P, P.tm0 + tm, tn, smem, s_d, s_x);
   store_partials<NWV>(P.partial, s_d, s_x, red_lds, threadIdx.x & 63, threadIdx.x >> 6, threadIdx.x);
 }
 
+// rows of the output that a launch computes (`first` a multiple of the tile's)
+struct Rows {
+  int64_t first, count;
+};
+
 template <class MM, int BM, int BN, int WM, int WN, int PF, int FLUSH, int MINW>
-static int64_t launch8(const GemmParams<typename MM::T>& P0, hipStream_t s) {
+static int64_t launch8(const GemmParams<typename MM::T>& P0, Rows rows, hipStream_t s) {
   using C = Gemm8Cfg<MM, BM, BN, WM, WN>;
   GemmParams<typename MM::T> P = P0;
-  P.tiles_m = (P.M + BM - 1) / BM;
+  P.tm0 = (int)(rows.first / BM);
+  P.tiles_m = (int)((rows.count + BM - 1) / BM);
   P.tiles_n = (P.N + BN - 1) / BN;
   const int64_t nt = (int64_t)P.tiles_m * P.tiles_n;
   if (nt == 0) return 0;
@@ -43,9 +49,10 @@ static int64_t launch8(const GemmParams<typename MM::T>& P0, hipStream_t s) {
 }
 
 template <class MM, int TM, int TN, int NWV, int PF, int MINW>
-static int64_t launch8_regs(const GemmParams<typename MM::T>& P0, hipStream_t s) {
+static int64_t launch8_regs(const GemmParams<typename MM::T>& P0, Rows rows, hipStream_t s) {
   GemmParams<typename MM::T> P = P0;
-  P.tiles_m = (P.M + 16 * TM - 1) / (16 * TM);
+  P.tm0 = (int)(rows.first / (16 * TM));
+  P.tiles_m = (int)((rows.count + 16 * TM - 1) / (16 * TM));
   P.tiles_n = (P.N + 16 * TN - 1) / (16 * TN);
   const int64_t nt = (int64_t)P.tiles_m * P.tiles_n;
   if (nt == 0) return 0;
@@ -57,7 +64,7 @@ static int64_t launch8_regs(const GemmParams<typename MM::T>& P0, hipStream_t s)
 template <class T>
 struct Entry8 {
   TileConfig cfg;
-  int64_t (*fn)(const GemmParams<T>&, hipStream_t);
+  int64_t (*fn)(const GemmParams<T>&, Rows, hipStream_t);
 };
 
 // Three tiles each: 64 x 64 (8 waves, one workgroup per compute unit) and 32 x 32 (4 waves, two per unit) through LDS, and
@@ -101,26 +108,73 @@ const std::vector<TileConfig>& eight_configs(Prec p) {
 //   K = 1000, 1000 x 1000: 64 x 64 300   32 x 32 346   16 x 16 377    (565)
 //   K = 4096, 4096 x 4096: 64 x 64 16830 32 x 32 19400                (30600; 65.3 TFLOP/s of MFMA work)
 // and FP32: 300^3 48 / 22 / 12 (41), 700^3 107 / 72 / 76 (138), 1000^3 162 / 195 / 234 (320), 4096^3 8720 / 10320 (15920).
-int eight_default(Prec p, int64_t M, int64_t N, int64_t K) {
-  struct Cost {
-    int64_t tile, cap;
-    double full, part, fixed;
-  };
+struct Cost {
+  int64_t tile, cap;
+  double full, part, fixed;
+};
+static const Cost& cost_of(Prec p, int cfg) {
   static constexpr Cost k64[3] = {{64, 256, 0.27, 0.27, 12}, {32, 512, 0.17, 0.094, 6}, {16, 512, 0.046, 0.025, 3}};
   static constexpr Cost k32[3] = {{64, 256, 0.14, 0.14, 10}, {32, 512, 0.095, 0.057, 5}, {16, 768, 0.041, 0.017, 3}};
+  return (p == P_F64E ? k64 : k32)[cfg];
+}
+static int64_t tiles_of(const Cost& c, int64_t M, int64_t N) { return ((M + c.tile - 1) / c.tile) * ((N + c.tile - 1) / c.tile); }
+static bool takes(Prec p, int cfg, int64_t K) { return !(p == P_F32E && cost_of(p, cfg).tile == 16 && K > kRegsMaxK); }
+static double launch_time(Prec p, int cfg, int64_t M, int64_t N, int64_t K) {
+  const Cost& c = cost_of(p, cfg);
+  const int64_t tiles = tiles_of(c, M, N), rest = tiles % c.cap;
+  return (double)K * ((double)(tiles / c.cap) * c.full + (rest == 0 ? 0.0 : rest <= 256 ? c.part : c.full)) + c.fixed;
+}
+
+// The launches of a configuration: its own tiles over all rows, or, where the model gives less, over the rows of its full
+// rounds, and smaller tiles over the rows that would be its nearly empty last round (N = M = K = 1536: 576 tiles of 64 x 64,
+// 2.25 rounds of 256; the FP32 solve of 2048 x 1536, whose products these are, 19.1 -> 16.1 ms).
+struct Split {
+  int64_t rows;  // of the configuration's own launch
+  int tail;      // configuration of the others
+  double time;
+};
+static Split split_of(Prec p, int cfg, int64_t M, int64_t N, int64_t K) {
+  Split best{M, -1, launch_time(p, cfg, M, N, K)};
+  const Cost& c = cost_of(p, cfg);
+  const int64_t tn = (N + c.tile - 1) / c.tile, rounds = tiles_of(c, M, N) / c.cap;
+  const int64_t rows = rounds > 0 ? rounds * c.cap / tn * c.tile : 0;
+  if (rows == 0 || rows >= M) return best;
+  const double own = launch_time(p, cfg, rows, N, K);
+  for (int t = cfg + 1; t < 3; ++t) {
+    if (!takes(p, t, K)) continue;
+    const double time = own + launch_time(p, t, M - rows, N, K);
+    if (time < 0.97 * best.time) best = Split{rows, t, time};
+  }
+  return best;
+}
+
+int eight_default(Prec p, int64_t M, int64_t N, int64_t K) {
   int best = 0;
   double best_t = 0.0;
   for (int i = 0; i < 3; ++i) {
-    const Cost& c = (p == P_F64E ? k64 : k32)[i];
-    if (p == P_F32E && c.tile == 16 && K > kRegsMaxK) continue;
-    const int64_t tiles = ((M + c.tile - 1) / c.tile) * ((N + c.tile - 1) / c.tile), rest = tiles % c.cap;
-    const double t = (double)K * ((double)(tiles / c.cap) * c.full + (rest == 0 ? 0.0 : rest <= 256 ? c.part : c.full)) + c.fixed;
+    if (!takes(p, i, K)) continue;
+    const double t = split_of(p, i, M, N, K).time;
     if (i == 0 || t < best_t) {
       best = i;
       best_t = t;
     }
   }
   return best;
+}
+
+int64_t eight_blocks(Prec p, int cfg, int64_t M, int64_t N, int64_t K) {
+  const Split sp = split_of(p, cfg, M, N, K);
+  return tiles_of(cost_of(p, cfg), sp.rows, N) + (sp.tail < 0 ? 0 : tiles_of(cost_of(p, sp.tail), M - sp.rows, N));
+}
+
+template <class T>
+static int64_t launch_split(Prec p, const std::vector<Entry8<T>>& table, const GemmParams<T>& P, int cfg, hipStream_t s) {
+  const Split sp = split_of(p, cfg, P.M, P.N, P.K);
+  const int64_t n = table[cfg].fn(P, Rows{0, sp.rows}, s);
+  if (sp.tail < 0) return n;
+  GemmParams<T> Q = P;
+  if (Q.partial) Q.partial += 2 * n;
+  return n + table[sp.tail].fn(Q, Rows{sp.rows, P.M - sp.rows}, s);
 }
 
 // Rows on 16-byte boundaries, lane offsets within a plane that fit 32 bits, and a K from which on the form's rounding error is
@@ -132,7 +186,7 @@ bool eight_fits(Prec p, const QView& A, const QView& B, int64_t M, int64_t K) {
   return al(A) && al(B) && M * A.ld * es < (int64_t(1) << 31) && 16 * B.ld * es < (int64_t(1) << 31) && K >= 16;
 }
 
-int64_t f64x8_launch(const GemmParams<double>& P, int cfg, hipStream_t s) { return f64_table8()[cfg].fn(P, s); }
-int64_t f32x8_launch(const GemmParams<float>& P, int cfg, hipStream_t s) { return f32_table8()[cfg].fn(P, s); }
+int64_t f64x8_launch(const GemmParams<double>& P, int cfg, hipStream_t s) { return launch_split(P_F64E, f64_table8(), P, cfg, s); }
+int64_t f32x8_launch(const GemmParams<float>& P, int cfg, hipStream_t s) { return launch_split(P_F32E, f32_table8(), P, cfg, s); }
 
 }  // namespace qp

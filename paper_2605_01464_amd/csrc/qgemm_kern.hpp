@@ -69,6 +69,7 @@ struct GemmParams {
   int64_t ldb, psb;
   int M, N, K;
   int tiles_m, tiles_n;
+  int tm0;  // first tile row of the launch (eight-product kernels)
   int vec;  // 16-byte vector loads allowed (aligned bases, ld and plane strides)
   int nout, nin, ref;
   T* out[3];

@@ -30,8 +30,10 @@ def _one_update(q, ctx, A, alpha, dtype):
     return to_np(X), {q.qpinv_tile_config_name(r["prec"], r["cfg"]) for r in rows}
 
 
-# square sizes around each tile's range, long and short K (the residual's side is the smaller dimension)
-SHAPES = [(1, 1), (2, 1), (15, 17), (16, 16), (33, 31), (129, 7), (9, 260), (65, 640), (701, 690), (1030, 1001), (2060, 40)]
+# square sizes around each tile's range, long and short K (the residual's side is the smaller dimension); the last two have
+# smaller tiles over the rows of the last round
+SHAPES = [(1, 1), (2, 1), (15, 17), (16, 16), (33, 31), (129, 7), (9, 260), (65, 640), (701, 690), (1030, 1001), (2060, 40),
+          (1100, 1090), (1043, 1300)]
 
 
 @pytest.mark.parametrize("dtype", ["f64", "f32"])
