@@ -83,7 +83,7 @@ __global__ void __launch_bounds__(256) norm_fit_kernel(const double* __restrict_
 // ------------------------------------------------------------------------------------------------
 // One training step (or one gradient) on a minibatch: a forward and backward pass with a wave per sample, then every
 // parameter's sum over the batch with a workgroup per row of a weight matrix.  (One workgroup for all of it walked the batch
-// through global memory phase by phase: 355 us at 256 samples; the two kernels take about 9 and 7.)
+// through global memory phase by phase: 355 us at 256 samples; the two kernels take about 8 and 6.)
 //
 // act layout: Z[B][F], H1[B][H], H2[B][H], D2[B][H], D1[B][H], dy[B], r[B]
 // ------------------------------------------------------------------------------------------------

@@ -1429,7 +1429,7 @@ int solve_batched(Ctx& c, int method, int order, int batch, const qpinv_qmat* A,
     c.batched_tuned[sig] = best_cfg;
   } else {
     // measured on the 512-matrix workload: phase-synchronous 32 x 32 x 32 tiles first, then the
-    // queue form with 64 x 64 tiles (batches above the phase-synchronous limit)
+    // queue form with 32 x 32 tiles (batches above the phase-synchronous limit)
     key.cfg = usable(kBatchedDefaultSync) ? kBatchedDefaultSync : kBatchedDefaultQueue;
   }
   run_batched(*c.batched, key, desc, order_v, alphas, out, s, c.opt.verbose != 0);
