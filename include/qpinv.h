@@ -410,7 +410,9 @@ int qpinv_qgemm_cfg(qpinv_ctx* ctx, int gemm_prec, int cfg, const qpinv_qmat* A,
  * (product precision x tile configuration) one row of 5 doubles is written to `out` (host):
  * {gemm_prec, tile configuration, launches, algorithmic flops (32 M N K each), summed event ms}.
  * The solvers' eight-product form of FP64 and FP32 (16 M N K operations executed) has the numbers behind the
- * type's tile configurations; qpinv_tile_config_name names them (f64x8_..., f32x8_...).
+ * type's tile configurations; qpinv_tile_config_name names them (f64x8_..., f32x8_...).  Its errors are relative to the
+ * norm of all four planes, so a matrix near a complex subalgebra (two planes below 1/5 of the other two in norm, or 1/16 in
+ * one row) is solved with the direct form, whose weak planes keep their own digits and whose zero planes stay zero.
  * At most max_rows rows; returns the number of rows (>= 0) or an error (EINVAL, EHIP).  The call
  * waits for the recorded events and resets the counters. */
 int qpinv_gemm_stats(qpinv_ctx* ctx, double* out, int max_rows);

@@ -5,6 +5,7 @@
 #include <cmath>
 
 #include "aux.hpp"
+#include "planes.hpp"
 #include "qgemm.hpp"
 
 namespace qp {
@@ -89,6 +90,12 @@ __device__ __forceinline__ double block_sum256(double v, double* sh) {
   const double r = sh[0];
   __syncthreads();
   return r;
+}
+
+__device__ __forceinline__ double wave_sum64(double x) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
+  return x;
 }
 
 __device__ __forceinline__ double block_max256(double v, double* sh) {
@@ -176,23 +183,29 @@ template void fill_pattern<float>(float*, int64_t, hipStream_t);
 template void fill_pattern<double>(double*, int64_t, hipStream_t);
 
 // ------------------------------------------------------------------------------------------------
-// norms: row pass (one workgroup per row), column pass (column strips x row blocks), finalize
+// norms: row pass (one workgroup per row), column pass (column strips x row blocks), finalize.  With `planes` the row pass also
+// leaves the sums of squares of the row's planes (planes[p m + i]) and, at planes[4 m + i], the bits of its planes that are not
+// zero, plus 16 if its planes are weak (planes.hpp).
 // ------------------------------------------------------------------------------------------------
 static int col_row_blocks(int64_t m) { return (int)std::max<int64_t>(1, std::min<int64_t>(64, (m + 63) / 64)); }
 
 template <class T>
 __global__ void __launch_bounds__(256) norms_row_kernel(const T* __restrict__ A, int64_t lda, int64_t psa, int n,
                                                         double* __restrict__ row_abs, double* __restrict__ row_sq,
-                                                        double* __restrict__ row_nf) {
+                                                        double* __restrict__ row_nf, double* __restrict__ planes) {
   __shared__ double sh[256];
   const int i = blockIdx.x;
-  double sa = 0.0, sq = 0.0, nf = 0.0;
+  double sa = 0.0, sq = 0.0, nf = 0.0, pl[4] = {0.0, 0.0, 0.0, 0.0};
+  unsigned nz = 0;
   for (int j = threadIdx.x; j < n; j += 256) {
     double q2 = 0.0;
+#pragma unroll
     for (int p = 0; p < 4; ++p) {
       const double v = (double)A[p * psa + (int64_t)i * lda + j];
       if (!isfinite(v)) nf += 1.0;
       q2 += v * v;
+      pl[p] += v * v;
+      nz |= v != 0.0 ? 1u << p : 0u;
     }
     sq += q2;
     sa += sqrt(q2);
@@ -204,6 +217,28 @@ __global__ void __launch_bounds__(256) norms_row_kernel(const T* __restrict__ A,
     row_abs[i] = sa;
     row_sq[i] = sq;
     row_nf[i] = nf;
+  }
+  if (planes == nullptr) return;
+  __shared__ double shp[4][4];
+  __shared__ unsigned shz[4];
+  const int w = threadIdx.x >> 6;
+  unsigned bits = 0;
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    const double t = wave_sum64(pl[p]);
+    if (__ballot((nz >> p) & 1u) != 0) bits |= 1u << p;
+    if ((threadIdx.x & 63) == 0) shp[w][p] = t;
+  }
+  if ((threadIdx.x & 63) == 0) shz[w] = bits;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double q[4];
+    for (int p = 0; p < 4; ++p) {
+      q[p] = ((shp[0][p] + shp[1][p]) + shp[2][p]) + shp[3][p];
+      planes[(int64_t)p * gridDim.x + i] = q[p];
+    }
+    bits = shz[0] | shz[1] | shz[2] | shz[3];
+    planes[4 * (int64_t)gridDim.x + i] = (double)(bits | (weak_planes(q[0], q[1], q[2], q[3], bits, kRowPairRatio) ? 16u : 0u));
   }
 }
 
@@ -260,7 +295,8 @@ __global__ void __launch_bounds__(256) norms_colmax_kernel(const double* __restr
 __global__ void __launch_bounds__(256) norms_final_kernel(const double* __restrict__ row_abs, const double* __restrict__ row_sq,
                                                           const double* __restrict__ row_nf, const double* __restrict__ col_part,
                                                           int m, int n, int nrb, const double* __restrict__ cmax_part,
-                                                          int ncmax, double* __restrict__ out) {
+                                                          int ncmax, const double* __restrict__ planes,
+                                                          double* __restrict__ out) {
   __shared__ double sh[256];
   double fro = 0.0, rmax = 0.0, nf = 0.0, cmax = 0.0;
   for (int i = threadIdx.x; i < m; i += 256) {
@@ -287,25 +323,40 @@ __global__ void __launch_bounds__(256) norms_final_kernel(const double* __restri
     out[2] = rmax;
     out[3] = nf;
   }
+  if (planes == nullptr) return;
+  __shared__ unsigned bits;
+  if (threadIdx.x == 0) bits = 0;
+  double q[4] = {0.0, 0.0, 0.0, 0.0};
+  unsigned mine = 0;
+  for (int i = threadIdx.x; i < m; i += 256) {
+#pragma unroll
+    for (int p = 0; p < 4; ++p) q[p] += planes[(int64_t)p * m + i];
+    mine |= (unsigned)planes[4 * (int64_t)m + i];
+  }
+  for (int p = 0; p < 4; ++p) q[p] = block_sum256(q[p], sh);
+  atomicOr(&bits, mine);
+  __syncthreads();
+  if (threadIdx.x == 0) out[4] = (bits & 16u) || weak_planes(q[0], q[1], q[2], q[3], bits, kPairRatio) ? 1.0 : 0.0;
 }
 
 int64_t norms_work_doubles(int64_t m, int64_t n) {
-  return 3 * m + (int64_t)col_row_blocks(m) * n + std::max<int64_t>(8, (n + 255) / 256);
+  return 8 * m + (int64_t)col_row_blocks(m) * n + std::max<int64_t>(8, (n + 255) / 256);
 }
 
 template <class T>
-void norms(const QView& A, int64_t m, int64_t n, double* out, double* work, hipStream_t s) {
+void norms(const QView& A, int64_t m, int64_t n, double* out, double* work, hipStream_t s, bool with_planes) {
   if (m == 0 || n == 0) {
-    zero_doubles(out, 4, s);
+    zero_doubles(out, with_planes ? 5 : 4, s);
     return;
   }
   double* row_abs = work;
   double* row_sq = work + m;
   double* row_nf = work + 2 * m;
-  double* col_part = work + 3 * m;
+  double* const planes = with_planes ? work + 3 * m : nullptr;
+  double* col_part = work + 8 * m;
   const int nrb = col_row_blocks(m);
   hipLaunchKernelGGL((norms_row_kernel<T>), dim3((unsigned)m), dim3(256), 0, s, static_cast<const T*>(A.p), A.ld, A.ps,
-                     (int)n, row_abs, row_sq, row_nf);
+                     (int)n, row_abs, row_sq, row_nf, planes);
   QP_HIP(hipGetLastError());
   if (wide_columns(n, nrb))
     hipLaunchKernelGGL((norms_col_kernel<T, 256>), dim3((unsigned)((n + 255) / 256), (unsigned)nrb), dim3(256), 0, s,
@@ -319,12 +370,12 @@ void norms(const QView& A, int64_t m, int64_t n, double* out, double* work, hipS
   if (ncmax > 0)
     hipLaunchKernelGGL(norms_colmax_kernel, dim3((unsigned)ncmax), dim3(256), 0, s, col_part, (int)n, nrb, cmax);
   hipLaunchKernelGGL(norms_final_kernel, dim3(1), dim3(256), 0, s, row_abs, row_sq, row_nf, col_part, (int)m, (int)n, nrb,
-                     cmax, ncmax, out);
+                     cmax, ncmax, planes, out);
   QP_HIP(hipGetLastError());
 }
 
-template void norms<float>(const QView&, int64_t, int64_t, double*, double*, hipStream_t);
-template void norms<double>(const QView&, int64_t, int64_t, double*, double*, hipStream_t);
+template void norms<float>(const QView&, int64_t, int64_t, double*, double*, hipStream_t, bool);
+template void norms<double>(const QView&, int64_t, int64_t, double*, double*, hipStream_t, bool);
 
 // ------------------------------------------------------------------------------------------------
 // power iteration on A^H A
@@ -354,12 +405,6 @@ __global__ void __launch_bounds__(256) sumsq_kernel(const double* __restrict__ x
     if (prev) prev[0] = out[0];
     out[0] = a;
   }
-}
-
-__device__ __forceinline__ double wave_sum64(double x) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
-  return x;
 }
 
 // w_i = (A v)_i / ||v||, v and w plane-major (4 x len).  ||v||^2 is summed from the elements a row's product reads anyway

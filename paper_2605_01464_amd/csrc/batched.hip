@@ -18,6 +18,7 @@
 
 #include "batched.hpp"
 #include "controller.hpp"
+#include "planes.hpp"
 #include "qgemm8_kern.hpp"
 
 namespace qp {
@@ -97,6 +98,19 @@ __device__ __forceinline__ double wg_sum(double v, double* sh) {
   return t;
 }
 
+// wave sums of four values (every lane gets them), the wave splitting them over its quarters first
+__device__ __forceinline__ void wave_planes(double (&v)[4]) {
+  const int lane = threadIdx.x & 63;
+  const bool hi = lane & 32, odd = lane & 16;
+  const double a = (hi ? v[2] : v[0]) + __shfl_xor(hi ? v[0] : v[2], 32, 64);
+  const double b = (hi ? v[3] : v[1]) + __shfl_xor(hi ? v[1] : v[3], 32, 64);
+  double r = (odd ? b : a) + __shfl_xor(odd ? a : b, 16, 64);
+#pragma unroll
+  for (int off = 8; off > 0; off >>= 1) r += __shfl_xor(r, off, 64);
+#pragma unroll
+  for (int p = 0; p < 4; ++p) v[p] = __shfl(r, 16 * p, 64);
+}
+
 // epilogue description for the in-workgroup product
 struct DEpi {
   int nout = 1;
@@ -119,9 +133,9 @@ __device__ __forceinline__ DEpi epi_out(const DM& o, float a = 1.f, float g = 0.
 }
 
 // Products of the 32 x 32 kernels with eight real products per quaternion product (qgemm8_kern.hpp): half the MFMAs of the
-// direct form, which stays where its rounding error is the smaller one (sums of fewer than 16 terms) and where an element's
-// sums with others could leave the type's range.  The choice is the matrix's, so every product of its solve and both kernel
-// forms take the same one.  Measured, 512 matrices of 32..256, QHPI19: the phase-synchronous form 17.95 -> 12.69 ms, of which
+// direct form, which stays where its rounding error is the smaller one (sums of fewer than 16 terms), where weak planes
+// would lose digits (planes.hpp) and where an element's sums with others could leave the type's range.  The choice is the
+// matrix's, so every product of its solve and both kernel forms take the same one.  Measured, 512 matrices of 32..256, QHPI19: the phase-synchronous form 17.95 -> 12.69 ms, of which
 // 0.98 are the set-up; an item of 10 K steps takes 19 us, a third of it outside the K loop.
 template <class MM, int BM, int BN, int WM, int WN>
 struct Eight {
@@ -133,8 +147,8 @@ struct Eight<MM16F, 32, 32, WM, WN> {
   static constexpr bool on = true;
   static constexpr int SMEM = 2 * Gemm8Cfg<MM16F, 32, 32, WM, WN>::STAGE;
 };
-__device__ __forceinline__ bool takes_eight(int m, int n, double normA) {
-  return min(m, n) >= 16 && normA > 1e-12 && normA < 1e12;
+__device__ __forceinline__ bool takes_eight(int m, int n, double normA, bool weak) {
+  return !weak && min(m, n) >= 16 && normA > 1e-12 && normA < 1e12;
 }
 
 // Tile t of a product (the eight-product form takes operands whose rows are 16-byte aligned).
@@ -404,19 +418,24 @@ __device__ __forceinline__ double power_fused(const DM& A, int steps, unsigned l
 // Per-matrix set-up by one workgroup: finiteness and ||A||_F, the scaling (power iteration on A^H A
 // from the SplitMix64 start vector, or the given alpha) and X_0 = alpha A^H into X0; A is also copied
 // to Ac unless Ac.p is null.  The power iteration keeps its vectors in `lds` (lds_floats floats) when
-// they fit, else in `dw` (4 (Dv + Dv) doubles with Dv >= max(m, n)).  Returns false (info.status =
-// ENONFINITE) for a non-finite A.
+// they fit, else in `dw` (4 (Dv + Dv) doubles with Dv >= max(m, n)).  `weak` (with PLANES): whether its planes are
+// (planes.hpp).  Returns false (info.status = ENONFINITE) for a non-finite A.
+template <bool PLANES>
 __device__ __forceinline__ bool setup_matrix(int scaling, int power_steps, unsigned long long seed, double alpha_given,
                                              const DM& A, const DM& Ac, const DM& X0, double* dw, int Dv, double* sh,
-                                             float* lds, int lds_floats, BInfo& info, double& normA, double& alpha) {
+                                             float* lds, int lds_floats, BInfo& info, double& normA, double& alpha,
+                                             bool& weak) {
   const int tid = threadIdx.x;
   const int nthr = blockDim.x;
   const int lane = tid & 63, nw = nthr >> 6;
   const int m = A.rows, n = A.cols;
   // one wave per row, lanes along the row: coalesced, 4 chunks of 64 columns in flight per wave
   constexpr int NG = 4;
-  double fro2 = 0.0, nf = 0.0;
+  double fro2 = 0.0, nf = 0.0, tot[4] = {0.0, 0.0, 0.0, 0.0};  // (tot: the planes' sums over this wave's rows)
+  unsigned seen = 0;  // its planes that are not zero, and 16 once a row's planes are weak
   for (int i = tid >> 6; i < m; i += nw) {
+    double pl[4] = {0.0, 0.0, 0.0, 0.0};
+    unsigned nz = 0;
     for (int j0 = 0; j0 < n; j0 += 64 * NG) {
       float a[NG][4];
 #pragma unroll
@@ -446,12 +465,41 @@ __device__ __forceinline__ bool setup_matrix(int scaling, int power_steps, unsig
           const double v = a[k][p];
           if (!__builtin_isfinite(v)) nf += 1.0;
           fro2 += v * v;
+          if constexpr (PLANES) {
+            pl[p] += v * v;
+            nz |= v != 0.0 ? 1u << p : 0u;
+          }
         }
       }
+    }
+    if constexpr (PLANES) {
+      wave_planes(pl);
+      unsigned bits = 0;
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        tot[p] += pl[p];
+        if (__ballot((nz >> p) & 1u) != 0) bits |= 1u << p;
+      }
+      seen |= bits | (weak_planes(pl[0], pl[1], pl[2], pl[3], bits, kRowPairRatio) ? 16u : 0u);
     }
   }
   fro2 = wg_sum(fro2, sh);
   nf = wg_sum(nf, sh);
+  if constexpr (PLANES) {
+    // the waves' flags as digits of base 32 (at most 16 waves), summed like the planes
+    double digits = 0.0;
+#pragma unroll
+    for (int p = 4; p >= 0; --p) digits = 32.0 * digits + (double)((seen >> p) & 1u);
+#pragma unroll
+    for (int p = 0; p < 4; ++p) tot[p] = wg_sum(lane == 0 ? tot[p] : 0.0, sh);
+    unsigned d = (unsigned)wg_sum(lane == 0 ? digits : 0.0, sh);
+    seen = 0;
+#pragma unroll
+    for (int p = 0; p < 5; ++p, d /= 32) seen |= d % 32 != 0 ? 1u << p : 0u;
+    weak = (seen & 16u) != 0 || weak_planes(tot[0], tot[1], tot[2], tot[3], seen, kPairRatio);
+  } else {
+    weak = false;
+  }
   if (nf > 0.0) {
     info.status = -2;
     return false;
@@ -686,16 +734,16 @@ __global__ void __launch_bounds__(64 * WM * WN) batched_kernel(BParams P) {
 
     DM X[4] = {buf(BX, n, m), buf(BX + 1, n, m), buf(BX + 2, n, m), buf(BX + 3, n, m)};
     double normA = 0.0, alpha = 0.0;
+    bool weak = false;
     DM Ac = buf(BE, m, n);  // the copy of A with 16-byte aligned rows, where the descriptor asks for one (free until the
     if (d.ldap == 0) Ac.p = nullptr;  // rise rule's candidate products, which end the solve)
-    if (!setup_matrix(P.scaling, P.power_steps, P.seed, P.scaling == 2 ? P.alpha[b] : 0.0, A, Ac, X[0], dw, D, sh, smem,
-                      C::SMEM,
-                      info, normA, alpha)) {
+    if (!setup_matrix<Eight<MM, BM, BN, WM, WN>::on>(P.scaling, P.power_steps, P.seed, P.scaling == 2 ? P.alpha[b] : 0.0, A, Ac,
+                                                     X[0], dw, D, sh, smem, C::SMEM, info, normA, alpha, weak)) {
       if (tid == 0) P.info[b] = info;
       continue;
     }
     if (Ac.p != nullptr) A = Ac;
-    const bool eight = takes_eight(m, n, normA);
+    const bool eight = takes_eight(m, n, normA, weak);
 
     // ---------------------------------------------------------------- iterations
     StopController ctl(P.stop, P.tol);
@@ -931,6 +979,7 @@ struct LState {
   int j;  // updates done; the current iterate is X_j
   int cur, best0, best1, best_j;
   int rsj0, rsj1;  // iterates whose residuals the R buffers 0 and 1 hold
+  int eight;  // its products take the eight-product form (takes_eight)
   unsigned int base;  // work items of this matrix completed before the current update (dataflow form)
   double alpha, normA, sigma1_sq, xn_prev, xn_a, xn_b, dx_rel;
   StopController ctl;
@@ -1349,8 +1398,10 @@ __global__ void __launch_bounds__(64 * WM * WN, PER_CU) batched_sync_kernel(SPar
     Ac.p = d.ldap > 0 ? B.base + 10 * 4 * d.pss + 5 * 4 * d.psw : nullptr;
     Ac.ld = d.ldap;
     Ac.ps = d.psap;
-    const bool ok = setup_matrix(P.scaling, P.power_steps, P.seed, P.scaling == 2 ? P.alpha[b] : 0.0, A, Ac, B.xw(0),
-                                 P.dwork + d.doff, Dv, sh, smem, C::SMEM, info, normA, alpha);
+    bool weak = false;
+    const bool ok = setup_matrix<Eight<MM, BM, BN, WM, WN>::on>(P.scaling, P.power_steps, P.seed,
+                                                                P.scaling == 2 ? P.alpha[b] : 0.0, A, Ac, B.xw(0), P.dwork + d.doff,
+                                                                Dv, sh, smem, C::SMEM, info, normA, alpha, weak);
     if (P.trace && tid == 0 && kTraceSetup + b < kTraceBusy) P.trace[kTraceSetup + b] = wall_clock64() - t_set;
     if (tid == 0) {
       LState S;
@@ -1366,6 +1417,7 @@ __global__ void __launch_bounds__(64 * WM * WN, PER_CU) batched_sync_kernel(SPar
       S.rsj0 = S.rsj1 = -1;
       S.alpha = alpha;
       S.normA = normA;
+      S.eight = takes_eight(d.m, d.n, normA, weak) ? 1 : 0;
       S.sigma1_sq = info.sigma1_sq;
       S.xn_prev = S.xn_a = S.xn_b = 0.0;
       S.base = 0u;
@@ -1541,7 +1593,7 @@ __global__ void __launch_bounds__(64 * WM * WN, PER_CU) batched_sync_kernel(SPar
           GemmParams<float> Gp = left ? gemm_params(Rr, Xr, eo, BM, BN) : gemm_params(Xr, Rr, eo, BM, BN);
           make_uniform(Gp);
           double a0 = 0.0, a1 = 0.0;
-          batch_tile<MM, BM, BN, BK, WM, WN, kLoadVec, true>(Gp, t, uni((int)takes_eight(d.m, d.n, S.normA)) != 0, smem, a0, a1);
+          batch_tile<MM, BM, BN, BK, WM, WN, kLoadVec, true>(Gp, t, uni(S.eight) != 0, smem, a0, a1);
           a0 = wg_sum(a0, sh);
           if (tid == 0) P.partial[d.poff + 2 * ((ph - 1) * tiles_of<BM, BN>(d.n, d.m) + t)] = a0;
           __syncthreads();
@@ -1576,7 +1628,7 @@ __global__ void __launch_bounds__(64 * WM * WN, PER_CU) batched_sync_kernel(SPar
           GemmParams<float> Gp = gemm_params(Aop, Bop, e, BM, BN);
           make_uniform(Gp);
           double a0 = 0.0, a1 = 0.0;
-          batch_tile<MM, BM, BN, BK, WM, WN, kLoadVec, true>(Gp, t, uni((int)takes_eight(d.m, d.n, S.normA)) != 0, smem, a0, a1);
+          batch_tile<MM, BM, BN, BK, WM, WN, kLoadVec, true>(Gp, t, uni(S.eight) != 0, smem, a0, a1);
           if (ph == np) {
             a0 = wg_sum(a0, sh);
             a1 = wg_sum(a1, sh);

@@ -15,7 +15,8 @@
 // ones (planes s and x), stay exactly real and complex.  What the form does not keep is the direct form's bound plane
 // by plane: its error is relative to the norm of all four planes.  An infinity, too, spreads as a NaN, and sums
 // overflow within a factor of two of the type's range.  The solvers use it, on operands they have checked (finite, of a
-// norm far inside the range); products that a caller asks for by themselves keep the direct form.
+// norm far inside the range, with planes of like size: planes.hpp); products that a caller asks for by themselves keep the
+// direct form.
 #pragma once
 
 #include "qgemm_kern.hpp"

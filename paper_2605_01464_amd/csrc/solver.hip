@@ -755,15 +755,15 @@ void x0_into(const Mat& A, double alpha, const Mat& X, hipStream_t s) {
     x0_scaled_adjoint<double, double>(A.v, A.rows, A.cols, alpha, X.v, s);
 }
 
-// norms of a matrix into host h[0..3] = {||M||_F^2, ||M||_1, ||M||_inf, nonfinite count}
-void norms_host(Ctx& c, const Mat& M, double h[4], hipStream_t s) {
+// norms of a matrix into host h[0..4] = {||M||_F^2, ||M||_1, ||M||_inf, nonfinite count, weak planes (planes.hpp)}
+void norms_host(Ctx& c, const Mat& M, double h[5], hipStream_t s) {
   double* work = static_cast<double*>(c.ws.get("normwork", sizeof(double) * norms_work_doubles(M.rows, M.cols)));
   if (M.dtype == QPINV_F32)
-    norms<float>(M.v, M.rows, M.cols, c.dsc + 8, work, s);
+    norms<float>(M.v, M.rows, M.cols, c.dsc + 8, work, s, true);
   else
-    norms<double>(M.v, M.rows, M.cols, c.dsc + 8, work, s);
-  to_host(c, c.dsc + 8, 4, s);
-  std::memcpy(h, c.hsc, sizeof(double) * 4);
+    norms<double>(M.v, M.rows, M.cols, c.dsc + 8, work, s, true);
+  to_host(c, c.dsc + 8, 5, s);
+  std::memcpy(h, c.hsc, sizeof(double) * 5);
 }
 
 double power_host(Ctx& c, const Mat& M, int steps, hipStream_t s, double* prev = nullptr) {
@@ -923,7 +923,7 @@ int solve(Ctx& c, int method, int order, const qpinv_qmat* Aq, int scaling, doub
     return Acache[k];
   };
 
-  double nh[4];
+  double nh[5];
   norms_host(c, A0, nh, s);
   if (nh[3] > 0) return finish(QPINV_ENONFINITE);
   const double normA = std::sqrt(nh[0]);
@@ -937,13 +937,14 @@ int solve(Ctx& c, int method, int order, const qpinv_qmat* Aq, int scaling, doub
 
   // Products with eight real products per quaternion product: A is finite, and with its norm this far inside the range (and
   // the iterates' with it, up to a condition number of 1e8 and more) no sum of two elements or of four products of them
-  // leaves it.  A solve that the one-launch path would take, but for its scaling or an option, keeps that path's direct
-  // form, so that all of them stop at the same update where the tolerance is the precision's floor.
+  // leaves it, and its planes are of like size, so that none loses digits that the direct form keeps (planes.hpp).  A solve that
+  // the one-launch path would take, but for its scaling or an option, keeps that path's direct form, so that all of them stop at
+  // the same update where the tolerance is the precision's floor.
   struct EightScope {
     Ctx& c;
     EightScope(Ctx& cx, bool on) : c(cx) { c.eight = on; }
     ~EightScope() { c.eight = false; }
-  } eight_scope(c, !small_takes(method, order, QPINV_ALPHA_POWER, stop, precision, m, n) &&
+  } eight_scope(c, nh[4] == 0.0 && !small_takes(method, order, QPINV_ALPHA_POWER, stop, precision, m, n) &&
                        normA > (precision == QPINV_PREC_F64 ? 1e-100 : 1e-12) &&
                        normA < (precision == QPINV_PREC_F64 ? 1e100 : 1e12));
 
@@ -1017,7 +1018,7 @@ int solve(Ctx& c, int method, int order, const qpinv_qmat* Aq, int scaling, doub
   IterSet* S = &set_of(dt);
   int cur = 0;
   if (scaling == QPINV_X0_GIVEN) {
-    double xh[4];
+    double xh[5];
     norms_host(c, Xout, xh, s);
     if (xh[3] > 0) return finish(QPINV_ENONFINITE);
     convert_mat(Xout, S->b[cur], s);
@@ -1525,7 +1526,7 @@ void residuals(Ctx& c, const qpinv_qmat* Aq, const qpinv_qmat* Xq, double E_abs[
 }
 
 void features(Ctx& c, const Mat& A, int steps, double out[7], hipStream_t s) {
-  double nh[4];
+  double nh[5];
   norms_host(c, A, nh, s);
   if (nh[3] > 0) throw Error(QPINV_ENONFINITE, "A holds NaN or Inf");
   out[0] = power_host(c, A, steps > 0 ? steps : c.opt.power_steps, s, &out[6]);
