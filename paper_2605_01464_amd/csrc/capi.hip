@@ -308,7 +308,7 @@ static int qgemm_impl(qpinv_ctx* c, int gemm_prec, int cfg, const qpinv_qmat* A,
       e.b[0][0] = beta;
     }
     const int64_t M = A->rows, N = B->cols, K = A->cols;
-    if (cfg < 0) cfg = cx.config_for((qp::Prec)gemm_prec, M, N, K, stream_of(hip_stream));
+    if (cfg < 0) cfg = cx.config_for((qp::Prec)gemm_prec, M, N, K, Am.v.ld, Bm.v.ld, stream_of(hip_stream));
     cx.flops += 32.0 * (double)M * (double)N * (double)K;
     qp::qgemm((qp::Prec)gemm_prec, Am.v, Bm.v, M, N, K, e, nullptr, cx.scratch, stream_of(hip_stream), cfg);
     return QPINV_OK;

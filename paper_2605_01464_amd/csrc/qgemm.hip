@@ -240,7 +240,7 @@ static void launch_any_mode(const GemmParams<typename MM::T>& P, int64_t grid, s
   constexpr bool ELEMS = BM * BK % C::NT == 0 && BK * BN % C::NT == 0;
   if (P.vec && P.M % BM == 0 && P.N % BN == 0 && P.K % BK == 0)
     launch_mode<MM, BM, BN, BK, WM, WN, FLUSH, DB, MINW, WALK, kLoadAligned>(P, grid, dyn_lds, s);
-  else if (ELEMS && P.M * P.lda < (int64_t(1) << 28) && BK * P.ldb < (int64_t(1) << 28))
+  else if (ELEMS && element_offsets(P.M, P.lda, BK, P.ldb))
     launch_mode<MM, BM, BN, BK, WM, WN, FLUSH, DB, MINW, WALK, ELEMS ? kLoadElems : kLoadScalar>(P, grid, dyn_lds, s);
   else if (P.vec)
     launch_mode<MM, BM, BN, BK, WM, WN, FLUSH, DB, MINW, WALK, kLoadVec>(P, grid, dyn_lds, s);
@@ -315,8 +315,6 @@ static const std::vector<F64Entry>& f64_table() {
 const std::vector<TileConfig>& bf16_configs();    // qgemm_bf16.hip
 const std::vector<TileConfig>& bf16x3_configs();  // qgemm_bf16.hip
 const std::vector<TileConfig>& eight_configs(Prec p);  // qgemm8.hip
-int eight_default(Prec p, int64_t M, int64_t N, int64_t K);
-int64_t eight_blocks(Prec p, int cfg, int64_t M, int64_t N, int64_t K);
 
 const std::vector<TileConfig>& tile_configs(Prec p) {
   static std::vector<TileConfig> f32, f64;
@@ -337,26 +335,6 @@ static int64_t blocks_for(const TileConfig& c, int64_t M, int64_t N) {
 int64_t qgemm_blocks(Prec p, int cfg, int64_t M, int64_t N) {
   const auto& t = tile_configs(p);
   return blocks_for(t.at(cfg), M, N);
-}
-
-// Measured on MI355X: the 64 x 64 double-buffered tiles win once there are >= 4 of them per compute unit,
-// the 32 x 32 ones below that (fewer tiles leave compute units idle in the last wave); for FP64 the 64 x 128
-// double-buffered tiles (8 waves of 32 x 32, twice the MFMA work per K-step barrier) beat 64 x 64 there
-// (4096^3: 30.8 vs 31.3 ms; 128 x 64 with the same waves 36.6 ms).  BF16 from 1024 tiles
-// of 64 x 64: the staged form with its operand tiles loaded straight into LDS; split BF16: 128 x 128 tiles
-// from 256 of them (one workgroup of 16 waves per CU), 64 x 64 below.  FP32 and FP64 products of other sizes than whole
-// tiles load element by element, and there the 32 x 32 tiles win at every size: they keep two workgroups per unit and
-// waste less at the edges (FP32 2049 x 2047 x 2045: 2.23 ms against 2.67, 4097^3: 16.8 against 17.4; FP64 4.45 against
-// 6.06, and 33.6 against 35.2).
-int default_config(Prec p, int64_t M, int64_t N, int64_t K) {
-  if (p == P_F64E || p == P_F32E) return eight_default(p, M, N, K);
-  const int64_t b64 = ((M + 63) / 64) * ((N + 63) / 64);
-  const bool whole = M % 64 == 0 && N % (p == P_F64 ? 128 : 64) == 0 && K % 16 == 0;
-  if (p == P_F64) return N <= 16 ? kNarrowConfig : b64 >= 1024 && whole ? 6 : 1;
-  if (p == P_BF16) return b64 >= 1024 ? 11 : b64 >= 256 ? 0 : 1;
-  if (p == P_BF16X3) return ((M + 127) / 128) * ((N + 127) / 128) >= 256 ? 4 : 3;
-  if (N <= 16) return kNarrowConfig;
-  return b64 >= 1024 && whole ? 5 : 6;
 }
 
 template <class T>
@@ -406,7 +384,7 @@ void qgemm(Prec p, const QView& A, const QView& B, int64_t M, int64_t N, int64_t
   if (M < 0 || N < 0 || K < 0) throw Error(-1, "qgemm: negative size");
   if (epi.nout < 1 || epi.nout > 3 || epi.nin < 0 || epi.nin > 3) throw Error(-1, "qgemm: bad epilogue");
   if (epi.reduce && (!red || epi.ref >= epi.nin)) throw Error(-1, "qgemm: bad reduction");
-  if (cfg < 0) cfg = default_config(p, M, N, K);
+  if (cfg < 0) cfg = default_config(p, M, N, K, A.ld, B.ld);
   const auto& cfgs = tile_configs(p);
   const bool narrow = cfg == kNarrowConfig && (p == P_F64 || p == P_F32) && N <= 16;
   if (cfg >= (int)cfgs.size() && !narrow) throw Error(-1, "qgemm: bad tile config");
@@ -419,7 +397,7 @@ void qgemm(Prec p, const QView& A, const QView& B, int64_t M, int64_t N, int64_t
   if (epi.reduce && nb > scratch.capacity / 2) throw Error(-1, "qgemm: reduction scratch too small");
   double* partial = epi.reduce ? scratch.partial : nullptr;
   int64_t launched = 0;
-  if ((p == P_F64E || p == P_F32E) && !eight_fits(p, A, B, M, K)) throw Error(-1, "qgemm: operands of the eight-product form");
+  if ((p == P_F64E || p == P_F32E) && !eight_fits(p, A, B, M, N, K)) throw Error(-1, "qgemm: operands of the eight-product form");
   if (narrow) {
     launched = M == 0 || N == 0 ? 0 : nb;
     if (launched > 0) {

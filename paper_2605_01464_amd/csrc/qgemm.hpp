@@ -15,12 +15,9 @@
 #include <vector>
 
 #include "common.hpp"
+#include "tilerule.hpp"
 
 namespace qp {
-
-// P_BF16X3: FP32 storage, each product as three BF16 products of split operands (hi.hi + hi.lo + lo.hi)
-// P_F64E, P_F32E: FP64 / FP32 with eight real products per quaternion product (qgemm8_kern.hpp); inside the solvers only
-enum Prec : int { P_F64 = 0, P_F32 = 1, P_BF16 = 2, P_BF16X3 = 3, P_F64E = 4, P_F32E = 5 };
 
 struct Epilogue {
   int nout = 1;
@@ -67,12 +64,6 @@ LaunchShape launch_shape(int64_t tiles, int per_cu, int occ, size_t static_lds);
 // F64 takes double storage).
 const std::vector<TileConfig>& tile_configs(Prec p);
 
-// The form for at most 16 columns (qgemm_narrow_kernel), outside the tables; its number in the product statistics
-constexpr int kNarrowConfig = 63;
-
-// Heuristic choice of tile configuration for a shape (used when no tuned choice exists).
-int default_config(Prec p, int64_t M, int64_t N, int64_t K);
-
 // Launch C = A B with the epilogue.  A is M x K, B is K x N, outputs/inputs M x N.
 // If epi.reduce, `red` (device, 2 doubles) receives {sum |out0 - in_ref|^2, sum |out0|^2}.
 // cfg < 0 selects the default configuration.
@@ -82,7 +73,7 @@ void qgemm(Prec p, const QView& A, const QView& B, int64_t M, int64_t N, int64_t
 // Number of workgroups a configuration launches for an M x N output (sizes scratch).
 int64_t qgemm_blocks(Prec p, int cfg, int64_t M, int64_t N);
 // whether the operands of an M x N x K product suit the eight-product form p (P_F64E, P_F32E)
-bool eight_fits(Prec p, const QView& A, const QView& B, int64_t M, int64_t K);
+bool eight_fits(Prec p, const QView& A, const QView& B, int64_t M, int64_t N, int64_t K);
 // whether a P_BF16X3 product of this shape fits the split copies' 32-bit buffer offsets
 bool bf16x3_fits(int64_t M, int64_t N, int64_t K);
 

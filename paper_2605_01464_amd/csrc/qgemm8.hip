@@ -79,7 +79,7 @@ static const std::vector<Entry8<double>>& f64_table8() {
 }
 
 // FP32 sums over k are flushed every 128 k, as in the direct form.  The register form does not flush: each wave sums a
-// quarter of k, which kRegsMaxK keeps at 512, the 128 dependent MFMAs that the direct form's 128 k take.
+// quarter of k, which kRegsMaxK (tilerule.hpp) keeps at 512, the 128 dependent MFMAs that the direct form's 128 k take.
 static const std::vector<Entry8<float>>& f32_table8() {
   static const std::vector<Entry8<float>> t = {
       {{0, 64, 64, 16, 1024, "f32x8_64x64_w4x4"}, launch8<MM16F, 64, 64, 4, 4, 1, 128, 4>},
@@ -88,7 +88,6 @@ static const std::vector<Entry8<float>>& f32_table8() {
   };
   return t;
 }
-constexpr int64_t kRegsMaxK = 2048;
 
 const std::vector<TileConfig>& eight_configs(Prec p) {
   auto list = [](const auto& table) {
@@ -98,73 +97,6 @@ const std::vector<TileConfig>& eight_configs(Prec p) {
   };
   static const std::vector<TileConfig> c64 = list(f64_table8()), c32 = list(f32_table8());
   return p == P_F64E ? c64 : c32;
-}
-
-// The tile that takes the least time by a model of rounds: with `cap` workgroups resident on the chip, every full round costs
-// full x K microseconds and the last, partial one `part` x K if it leaves at most one workgroup per unit.  Measured, FP64 (us):
-//   K = 300, 300 x 300:    64 x 64 90    32 x 32 34    16 x 16 19     (direct form 55)
-//   K = 1000, 500 x 500:   64 x 64 267   32 x 32 100   16 x 16 94     (170)
-//   K = 700, 700 x 700:    64 x 64 197   32 x 32 128   16 x 16 142    (208)
-//   K = 1000, 1000 x 1000: 64 x 64 300   32 x 32 346   16 x 16 377    (565)
-//   K = 4096, 4096 x 4096: 64 x 64 16830 32 x 32 19400                (30600; 65.3 TFLOP/s of MFMA work)
-// and FP32: 300^3 48 / 22 / 12 (41), 700^3 107 / 72 / 76 (138), 1000^3 162 / 195 / 234 (320), 4096^3 8720 / 10320 (15920).
-struct Cost {
-  int64_t tile, cap;
-  double full, part, fixed;
-};
-static const Cost& cost_of(Prec p, int cfg) {
-  static constexpr Cost k64[3] = {{64, 256, 0.27, 0.27, 12}, {32, 512, 0.17, 0.094, 6}, {16, 512, 0.046, 0.025, 3}};
-  static constexpr Cost k32[3] = {{64, 256, 0.14, 0.14, 10}, {32, 512, 0.095, 0.057, 5}, {16, 768, 0.041, 0.017, 3}};
-  return (p == P_F64E ? k64 : k32)[cfg];
-}
-static int64_t tiles_of(const Cost& c, int64_t M, int64_t N) { return ((M + c.tile - 1) / c.tile) * ((N + c.tile - 1) / c.tile); }
-static bool takes(Prec p, int cfg, int64_t K) { return !(p == P_F32E && cost_of(p, cfg).tile == 16 && K > kRegsMaxK); }
-static double launch_time(Prec p, int cfg, int64_t M, int64_t N, int64_t K) {
-  const Cost& c = cost_of(p, cfg);
-  const int64_t tiles = tiles_of(c, M, N), rest = tiles % c.cap;
-  return (double)K * ((double)(tiles / c.cap) * c.full + (rest == 0 ? 0.0 : rest <= 256 ? c.part : c.full)) + c.fixed;
-}
-
-// The launches of a configuration: its own tiles over all rows, or, where the model gives less, over the rows of its full
-// rounds, and smaller tiles over the rows that would be its nearly empty last round (N = M = K = 1536: 576 tiles of 64 x 64,
-// 2.25 rounds of 256; the FP32 solve of 2048 x 1536, whose products these are, 19.1 -> 16.1 ms).
-struct Split {
-  int64_t rows;  // of the configuration's own launch
-  int tail;      // configuration of the others
-  double time;
-};
-static Split split_of(Prec p, int cfg, int64_t M, int64_t N, int64_t K) {
-  Split best{M, -1, launch_time(p, cfg, M, N, K)};
-  const Cost& c = cost_of(p, cfg);
-  const int64_t tn = (N + c.tile - 1) / c.tile, rounds = tiles_of(c, M, N) / c.cap;
-  const int64_t rows = rounds > 0 ? rounds * c.cap / tn * c.tile : 0;
-  if (rows == 0 || rows >= M) return best;
-  const double own = launch_time(p, cfg, rows, N, K);
-  for (int t = cfg + 1; t < 3; ++t) {
-    if (!takes(p, t, K)) continue;
-    const double time = own + launch_time(p, t, M - rows, N, K);
-    if (time < 0.97 * best.time) best = Split{rows, t, time};
-  }
-  return best;
-}
-
-int eight_default(Prec p, int64_t M, int64_t N, int64_t K) {
-  int best = 0;
-  double best_t = 0.0;
-  for (int i = 0; i < 3; ++i) {
-    if (!takes(p, i, K)) continue;
-    const double t = split_of(p, i, M, N, K).time;
-    if (i == 0 || t < best_t) {
-      best = i;
-      best_t = t;
-    }
-  }
-  return best;
-}
-
-int64_t eight_blocks(Prec p, int cfg, int64_t M, int64_t N, int64_t K) {
-  const Split sp = split_of(p, cfg, M, N, K);
-  return tiles_of(cost_of(p, cfg), sp.rows, N) + (sp.tail < 0 ? 0 : tiles_of(cost_of(p, sp.tail), M - sp.rows, N));
 }
 
 template <class T>
@@ -179,11 +111,12 @@ static int64_t launch_split(Prec p, const std::vector<Entry8<T>>& table, const G
 
 // Rows on 16-byte boundaries, lane offsets within a plane that fit 32 bits, and a K from which on the form's rounding error is
 // the smaller one (FP32, sequential sums, iid planes: 1.12e-7 against the direct form's 1.08e-7 at K = 8, 1.69e-7 against
-// 2.09e-7 at K = 32).
-bool eight_fits(Prec p, const QView& A, const QView& B, int64_t M, int64_t K) {
+// 2.09e-7 at K = 32).  And an output whose partial sums fit the scratch, at least by the largest tiles.
+bool eight_fits(Prec p, const QView& A, const QView& B, int64_t M, int64_t N, int64_t K) {
   const int64_t es = p == P_F64E ? 8 : 4, va = 16 / es;
   auto al = [&](const QView& v) { return (reinterpret_cast<uintptr_t>(v.p) & 15) == 0 && v.ld % va == 0 && v.ps % va == 0; };
-  return al(A) && al(B) && M * A.ld * es < (int64_t(1) << 31) && 16 * B.ld * es < (int64_t(1) << 31) && K >= 16;
+  return al(A) && al(B) && M * A.ld * es < (int64_t(1) << 31) && 16 * B.ld * es < (int64_t(1) << 31) && K >= 16 &&
+         eight_takes(p, 0, M, N, K);
 }
 
 int64_t f64x8_launch(const GemmParams<double>& P, int cfg, hipStream_t s) { return launch_split(P_F64E, f64_table8(), P, cfg, s); }

@@ -110,7 +110,7 @@ void Workspace::release() {
 
 Ctx::Ctx(int dev) : device(dev) {
   QP_HIP(hipSetDevice(dev));
-  scratch.capacity = 1 << 20;
+  scratch.capacity = 2 * kMaxPartials;
   QP_HIP(hipMalloc(&scratch.partial, sizeof(double) * scratch.capacity));
   QP_HIP(hipMalloc(&dsc, sizeof(double) * 64));
   QP_HIP(hipHostMalloc(&hsc, sizeof(double) * 64, hipHostMallocDefault));
@@ -136,12 +136,12 @@ Ctx::~Ctx() {
   if (hstage) (void)hipHostFree(hstage);
 }
 
-int Ctx::config_for(Prec p, int64_t M, int64_t N, int64_t K, hipStream_t s) {
+int Ctx::config_for(Prec p, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, hipStream_t s) {
   if (p <= P_BF16X3 && opt.force_cfg[(int)p] >= 0) return opt.force_cfg[(int)p];
   auto key = std::make_tuple((int)p, M, N, K);
   auto it = tuned.find(key);
   if (it != tuned.end()) return it->second;
-  const int def = default_config(p, M, N, K);
+  const int def = default_config(p, M, N, K, lda, ldb);
   if (def != kNarrowConfig && opt.autotune && !no_alloc) return autotune(*this, p, M, N, K, nullptr, s);
   return def;
 }
@@ -189,10 +189,10 @@ void gemm(Ctx& c, Prec p, const Mat& A, const Mat& B, const Epilogue& e, hipStre
   // a tile configuration of the direct form that the caller asks for (gemm_cfg_*) is taken as it is
   if (c.eight && (p == P_F64 || p == P_F32) && c.opt.force_cfg[(int)p] < 0) {
     const Prec p8 = p == P_F64 ? P_F64E : P_F32E;
-    if (eight_fits(p8, A.v, B.v, M, K)) p = p8;
+    if (eight_fits(p8, A.v, B.v, M, N, K)) p = p8;
   }
   const bool eight = p == P_F64E || p == P_F32E;
-  const int cfg = c.config_for(p, M, N, K, s);
+  const int cfg = c.config_for(p, M, N, K, A.v.ld, B.v.ld, s);
   const double f = 32.0 * (double)M * (double)N * (double)K;
   c.flops += f;
   if (!c.opt.gemm_timing || c.no_alloc) {
@@ -1556,7 +1556,7 @@ int autotune(Ctx& c, Prec p, int64_t M, int64_t N, int64_t K, double* best_ms, h
   hipEvent_t e0, e1;
   QP_HIP(hipEventCreate(&e0));
   QP_HIP(hipEventCreate(&e1));
-  const bool narrow = default_config(p, M, N, K) == kNarrowConfig;  // stays the choice where it applies: no tile is faster
+  const bool narrow = default_config(p, M, N, K, A.v.ld, B.v.ld) == kNarrowConfig;  // stays the choice where it applies: no tile is faster
   int best = 0;
   double best_t = 1e300;
   // two timed rounds over all configurations (the first also warms clocks and caches); a

@@ -90,7 +90,7 @@ struct Ctx {
 
   explicit Ctx(int dev);
   ~Ctx();
-  int config_for(Prec p, int64_t M, int64_t N, int64_t K, hipStream_t s);
+  int config_for(Prec p, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, hipStream_t s);
 };
 
 // A quaternion matrix with its shape and element type.
