@@ -387,7 +387,7 @@ int qpinv_autotune(qpinv_ctx* ctx, int gemm_prec, int64_t M, int64_t N, int64_t 
  * EINVAL (no path, file not writable).  qpinv_tune_load merges such a file into this context's tuned
  * choices (an entry for the same shape or signature replaces the context's) and returns the number of
  * entries applied: 0 for a file written on another device; entries naming a configuration this library
- * does not have are skipped.  EINVAL for no path, an unreadable file or a malformed one (then nothing is
+ * does not have, or does not use for that shape, are skipped.  EINVAL for no path, an unreadable file or a malformed one (then nothing is
  * applied).  Neither call uses the GPU beyond reading the device's properties. */
 int qpinv_tune_save(qpinv_ctx* ctx, const char* path);
 int qpinv_tune_load(qpinv_ctx* ctx, const char* path);

@@ -559,7 +559,7 @@ int qpinv_tune_load(qpinv_ctx* c, const char* path) {
     std::string err;
     if (!qp::tune_parse(text, f, err)) throw qp::Error(QPINV_EINVAL, err);
     if (f.device != tune_device(cx.device)) return 0;
-    // names to indices; entries whose configuration this library does not have are skipped
+    // names to indices; entries whose configuration this library does not have, or not for the shape, are skipped
     int applied = 0;
     for (const auto& g : f.gemm) {
       const int p = std::get<0>(g);
@@ -567,6 +567,10 @@ int qpinv_tune_load(qpinv_ctx* c, const char* path) {
         const auto& t = qp::tile_configs((qp::Prec)q);
         const auto hit = std::find_if(t.begin(), t.end(), [&](const qp::TileConfig& x) { return std::get<4>(g) == x.name; });
         if (hit == t.end()) continue;
+        const int64_t M = std::get<1>(g), N = std::get<2>(g), K = std::get<3>(g);
+        if (std::max({M, N, K}) <= qp::kMaxSide &&  // (larger ones are never looked up)
+            !qp::config_takes((qp::Prec)q, (int)(hit - t.begin()), M, N, K))
+          break;
         cx.tuned[std::make_tuple(q, std::get<1>(g), std::get<2>(g), std::get<3>(g))] = (int)(hit - t.begin());
         ++applied;
         break;

@@ -379,6 +379,20 @@ int64_t bf16x3_blocks(int cfg, int64_t M, int64_t N);
 int64_t f64x8_launch(const GemmParams<double>& P, int cfg, hipStream_t s);  // qgemm8.hip
 int64_t f32x8_launch(const GemmParams<float>& P, int cfg, hipStream_t s);
 
+// an upper bound of the workgroups a configuration launches (a per-CU configuration launches at most this many)
+static int64_t config_blocks(Prec p, int cfg, int64_t M, int64_t N, int64_t K) {
+  if (cfg == kNarrowConfig) return (M + 15) / 16;
+  if (p == P_BF16) return bf16_blocks(cfg, M, N);
+  if (p == P_BF16X3) return bf16x3_blocks(cfg, M, N);
+  if (p == P_F64E || p == P_F32E) return eight_blocks(p, cfg, M, N, K);
+  return blocks_for(tile_configs(p)[cfg], M, N);
+}
+
+bool config_takes(Prec p, int cfg, int64_t M, int64_t N, int64_t K) {
+  if (p == P_F64E || p == P_F32E) return eight_takes(p, cfg, M, N, K);
+  return config_blocks(p, cfg, M, N, K) <= kMaxPartials;
+}
+
 void qgemm(Prec p, const QView& A, const QView& B, int64_t M, int64_t N, int64_t K, const Epilogue& epi,
            double* red, GemmScratch& scratch, hipStream_t stream, int cfg) {
   if (M < 0 || N < 0 || K < 0) throw Error(-1, "qgemm: negative size");
@@ -388,16 +402,11 @@ void qgemm(Prec p, const QView& A, const QView& B, int64_t M, int64_t N, int64_t
   const auto& cfgs = tile_configs(p);
   const bool narrow = cfg == kNarrowConfig && (p == P_F64 || p == P_F32) && N <= 16;
   if (cfg >= (int)cfgs.size() && !narrow) throw Error(-1, "qgemm: bad tile config");
-  // an upper bound of the workgroups launched (a per-CU configuration launches at most this many)
-  const int64_t nb = narrow          ? (M + 15) / 16
-                     : p == P_BF16     ? bf16_blocks(cfg, M, N)
-                     : p == P_BF16X3 ? bf16x3_blocks(cfg, M, N)
-                     : p == P_F64E || p == P_F32E ? eight_blocks(p, cfg, M, N, K)
-                                     : blocks_for(cfgs[cfg], M, N);
+  const int64_t nb = config_blocks(p, cfg, M, N, K);
   if (epi.reduce && nb > scratch.capacity / 2) throw Error(-1, "qgemm: reduction scratch too small");
   double* partial = epi.reduce ? scratch.partial : nullptr;
   int64_t launched = 0;
-  if ((p == P_F64E || p == P_F32E) && !eight_fits(p, A, B, M, N, K)) throw Error(-1, "qgemm: operands of the eight-product form");
+  if ((p == P_F64E || p == P_F32E) && !(eight_fits(p, A, B, M, N, K) && eight_takes(p, cfg, M, N, K))) throw Error(-1, "qgemm: operands of the eight-product form");
   if (narrow) {
     launched = M == 0 || N == 0 ? 0 : nb;
     if (launched > 0) {

@@ -72,6 +72,9 @@ void qgemm(Prec p, const QView& A, const QView& B, int64_t M, int64_t N, int64_t
 
 // Number of workgroups a configuration launches for an M x N output (sizes scratch).
 int64_t qgemm_blocks(Prec p, int cfg, int64_t M, int64_t N);
+// whether a configuration may be kept for every product of a shape: its partial sums fit the scratch, and K is within the
+// limit of a form that does not flush its sums
+bool config_takes(Prec p, int cfg, int64_t M, int64_t N, int64_t K);
 // whether the operands of an M x N x K product suit the eight-product form p (P_F64E, P_F32E)
 bool eight_fits(Prec p, const QView& A, const QView& B, int64_t M, int64_t N, int64_t K);
 // whether a P_BF16X3 product of this shape fits the split copies' 32-bit buffer offsets

@@ -163,7 +163,7 @@ void validate(const qpinv_qmat* q, const char* what) {
   if (!q) throw Error(QPINV_EINVAL, std::string(what) + ": null descriptor");
   if (q->dtype != QPINV_F32 && q->dtype != QPINV_F64) throw Error(QPINV_EINVAL, std::string(what) + ": bad dtype");
   if (q->rows < 0 || q->cols < 0) throw Error(QPINV_EINVAL, std::string(what) + ": negative shape");
-  if (q->rows > (1 << 20) || q->cols > (1 << 20)) throw Error(QPINV_EINVAL, std::string(what) + ": shape too large");
+  if (q->rows > kMaxSide || q->cols > kMaxSide) throw Error(QPINV_EINVAL, std::string(what) + ": shape too large");
   if (q->ld < q->cols || q->ld < 1) throw Error(QPINV_EINVAL, std::string(what) + ": ld < cols");
   if (q->plane_stride < q->rows * q->ld) throw Error(QPINV_EINVAL, std::string(what) + ": plane_stride < rows*ld");
   if (q->rows > 0 && q->cols > 0 && !q->data) throw Error(QPINV_EINVAL, std::string(what) + ": null data");
@@ -1538,7 +1538,7 @@ void features(Ctx& c, const Mat& A, int steps, double out[7], hipStream_t s) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// autotuner: time every tile configuration on the shape, keep the fastest
+// autotuner: time every tile configuration that the shape takes (all, if it takes none), keep the fastest
 // ------------------------------------------------------------------------------------------------
 int autotune(Ctx& c, Prec p, int64_t M, int64_t N, int64_t K, double* best_ms, hipStream_t s) {
   if (M < 1 || N < 1 || K < 1) throw Error(QPINV_EINVAL, "autotune: empty shape");
@@ -1559,12 +1559,17 @@ int autotune(Ctx& c, Prec p, int64_t M, int64_t N, int64_t K, double* best_ms, h
   const bool narrow = default_config(p, M, N, K, A.v.ld, B.v.ld) == kNarrowConfig;  // stays the choice where it applies: no tile is faster
   int best = 0;
   double best_t = 1e300;
+  std::vector<int> cfgs;
+  for (int cfg = 0; cfg < ncfg; ++cfg)
+    if (config_takes(p, cfg, M, N, K)) cfgs.push_back(cfg);
+  if (cfgs.empty())
+    for (int cfg = 0; cfg < ncfg; ++cfg) cfgs.push_back(cfg);
   // two timed rounds over all configurations (the first also warms clocks and caches); a
   // configuration's time is its faster round
   const int reps = 3;
   std::vector<double> tbest(ncfg, 1e300);
   for (int round = 0; round < 2; ++round)
-    for (int cfg = 0; cfg < ncfg; ++cfg) {
+    for (int cfg : cfgs) {
       qgemm(p, A.v, B.v, M, N, K, epi1(C), nullptr, c.scratch, s, cfg);  // warm-up
       QP_HIP(hipEventRecord(e0, s));
       for (int r = 0; r < reps; ++r) qgemm(p, A.v, B.v, M, N, K, epi1(C), nullptr, c.scratch, s, cfg);
@@ -1574,7 +1579,7 @@ int autotune(Ctx& c, Prec p, int64_t M, int64_t N, int64_t K, double* best_ms, h
       QP_HIP(hipEventElapsedTime(&ms, e0, e1));
       tbest[cfg] = std::min(tbest[cfg], (double)ms / reps);
     }
-  for (int cfg = 0; cfg < ncfg; ++cfg) {
+  for (int cfg : cfgs) {
     const double t = tbest[cfg];
     if (c.opt.verbose) fprintf(stderr, "[qpinv] tune %s %ldx%ldx%ld: %.4f ms\n", tile_configs(p)[cfg].name, (long)M, (long)N, (long)K, t);
     if (t < best_t) {

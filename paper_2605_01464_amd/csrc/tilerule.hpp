@@ -12,6 +12,8 @@ enum Prec : int { P_F64 = 0, P_F32 = 1, P_BF16 = 2, P_BF16X3 = 3, P_F64E = 4, P_
 // The form for at most 16 columns (qgemm_narrow_kernel), outside the tables; its number in the product statistics
 constexpr int kNarrowConfig = 63;
 
+constexpr int64_t kMaxSide = int64_t(1) << 20;  // rows and columns of a matrix that the library accepts
+
 // Largest number of workgroups (pairs of partial sums) of a product with a reduction; the context's scratch has this room
 constexpr int64_t kMaxPartials = int64_t(1) << 19;
 
