@@ -374,9 +374,11 @@ int qpinv_spectral_labels(qpinv_ctx* ctx, int method, int order, const double* s
                           const double* s1sq_est, double tol, int max_iter, int ngrid, double mu_lo, double mu_hi,
                           double mu_target, double* mu_out, int* j_best, int* j_classical, void* hip_stream);
 
-/* Time every tile configuration of the product for shape (M, N, K) in `gemm_prec` and remember the
- * fastest for later solves on this context.  best_ms (host, may be NULL) receives its time.
- * Returns the chosen configuration id (>= 0) or an error. */
+/* Time every tile configuration of the product for shape (M, N, K) in `gemm_prec` (for N <= 16 the narrow form
+ * too) and remember the fastest for this context's later products of that precision and shape.  best_ms (host, may be NULL)
+ * receives its time.  Returns the chosen configuration id (>= 0) or an error.  Solves whose FP64 or FP32 products take
+ * the eight-product form (qpinv_gemm_stats) choose that form's tiles by themselves: by rule, or timed and remembered
+ * with option autotune = 1. */
 int qpinv_autotune(qpinv_ctx* ctx, int gemm_prec, int64_t M, int64_t N, int64_t K, double* best_ms,
                    void* hip_stream);
 
@@ -401,7 +403,8 @@ const char* qpinv_tile_config_name(int gemm_prec, int cfg);
 int qpinv_num_batched_configs(void);
 const char* qpinv_batched_config_name(int cfg);
 
-/* Same as qpinv_qgemm with an explicit tile configuration (for measurement). */
+/* Same as qpinv_qgemm with an explicit tile configuration, one of the table or the one that qpinv_autotune chose for the
+ * shape (for measurement). */
 int qpinv_qgemm_cfg(qpinv_ctx* ctx, int gemm_prec, int cfg, const qpinv_qmat* A, const qpinv_qmat* B,
                     qpinv_qmat* C, double alpha, double beta, double gamma, void* hip_stream);
 

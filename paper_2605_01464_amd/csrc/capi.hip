@@ -295,7 +295,8 @@ static int qgemm_impl(qpinv_ctx* c, int gemm_prec, int cfg, const qpinv_qmat* A,
     if (A->cols != B->rows || C->rows != A->rows || C->cols != B->cols) throw qp::Error(QPINV_EINVAL, "qgemm: shape mismatch");
     if (C->data && (C->data == A->data || C->data == B->data)) throw qp::Error(QPINV_EINVAL, "qgemm: C aliases an operand");
     const int ncfg = (int)qp::tile_configs((qp::Prec)gemm_prec).size();
-    if (cfg >= ncfg) throw qp::Error(QPINV_EINVAL, "qgemm: bad tile configuration");
+    if (cfg >= ncfg && !(cfg == qp::kNarrowConfig && qp::config_takes((qp::Prec)gemm_prec, cfg, A->rows, B->cols, A->cols)))
+      throw qp::Error(QPINV_EINVAL, "qgemm: bad tile configuration");
     const qp::Mat Am = qp::from_abi(*A), Bm = qp::from_abi(*B), Cm = qp::from_abi(*C);
     qp::Epilogue e;
     e.nout = 1;
@@ -537,7 +538,7 @@ int qpinv_tune_save(qpinv_ctx* c, const char* path) {
       // the eight-product forms under the type's own number: their configuration names tell them apart
       const int pt = p == qp::P_F64E ? qp::P_F64 : p == qp::P_F32E ? qp::P_F32 : p;
       f.gemm.emplace_back(pt, std::get<1>(e.first), std::get<2>(e.first), std::get<3>(e.first),
-                          qp::tile_configs((qp::Prec)p).at(e.second).name);
+                          qp::config_name((qp::Prec)p, e.second));
     }
     for (const auto& e : cx.batched_tuned) f.batched.emplace_back(e.first, qp::batched_config_name(e.second));
     std::ofstream out(path, std::ios::binary | std::ios::trunc);
@@ -564,14 +565,16 @@ int qpinv_tune_load(qpinv_ctx* c, const char* path) {
     for (const auto& g : f.gemm) {
       const int p = std::get<0>(g);
       for (int q : {p, p == qp::P_F64 ? (int)qp::P_F64E : p == qp::P_F32 ? (int)qp::P_F32E : p}) {
-        const auto& t = qp::tile_configs((qp::Prec)q);
-        const auto hit = std::find_if(t.begin(), t.end(), [&](const qp::TileConfig& x) { return std::get<4>(g) == x.name; });
-        if (hit == t.end()) continue;
         const int64_t M = std::get<1>(g), N = std::get<2>(g), K = std::get<3>(g);
-        if (std::max({M, N, K}) <= qp::kMaxSide &&  // (larger ones are never looked up)
-            !qp::config_takes((qp::Prec)q, (int)(hit - t.begin()), M, N, K))
-          break;
-        cx.tuned[std::make_tuple(q, std::get<1>(g), std::get<2>(g), std::get<3>(g))] = (int)(hit - t.begin());
+        int cfg = qp::kNarrowConfig;
+        if (std::get<4>(g) != qp::config_name((qp::Prec)q, cfg)) {
+          const auto& t = qp::tile_configs((qp::Prec)q);
+          const auto hit = std::find_if(t.begin(), t.end(), [&](const qp::TileConfig& x) { return std::get<4>(g) == x.name; });
+          if (hit == t.end()) continue;
+          cfg = (int)(hit - t.begin());
+        }
+        if (std::max({M, N, K}) <= qp::kMaxSide && !qp::config_takes((qp::Prec)q, cfg, M, N, K)) break;  // (larger: never looked up)
+        cx.tuned[std::make_tuple(q, M, N, K)] = cfg;
         ++applied;
         break;
       }
@@ -595,7 +598,7 @@ int qpinv_num_tile_configs(int gemm_prec) {
 const char* qpinv_tile_config_name(int gemm_prec, int cfg) {
   if (gemm_prec < QPINV_GEMM_F64 || gemm_prec > QPINV_GEMM_BF16X3) return "";
   const auto& t = qp::tile_configs((qp::Prec)gemm_prec);
-  if (cfg == qp::kNarrowConfig && gemm_prec <= QPINV_GEMM_F32) return gemm_prec == QPINV_GEMM_F64 ? "f64_16x16_narrow" : "f32_16x16_narrow";
+  if (cfg == qp::kNarrowConfig) return qp::config_name((qp::Prec)gemm_prec, cfg);
   if (cfg >= (int)t.size() && gemm_prec <= QPINV_GEMM_F32) {  // as the product statistics number the eight-product form
     const auto& e = qp::tile_configs(gemm_prec == QPINV_GEMM_F64 ? qp::P_F64E : qp::P_F32E);
     return cfg - (int)t.size() < (int)e.size() ? e[cfg - t.size()].name : "";

@@ -388,7 +388,14 @@ static int64_t config_blocks(Prec p, int cfg, int64_t M, int64_t N, int64_t K) {
   return blocks_for(tile_configs(p)[cfg], M, N);
 }
 
+const char* config_name(Prec p, int cfg) {
+  if (cfg == kNarrowConfig && (p == P_F64 || p == P_F32)) return p == P_F64 ? "f64_16x16_narrow" : "f32_16x16_narrow";
+  const auto& t = tile_configs(p);
+  return cfg >= 0 && cfg < (int)t.size() ? t[cfg].name : "";
+}
+
 bool config_takes(Prec p, int cfg, int64_t M, int64_t N, int64_t K) {
+  if (cfg == kNarrowConfig && (N > 16 || (p != P_F64 && p != P_F32))) return false;
   if (p == P_F64E || p == P_F32E) return eight_takes(p, cfg, M, N, K);
   return config_blocks(p, cfg, M, N, K) <= kMaxPartials;
 }

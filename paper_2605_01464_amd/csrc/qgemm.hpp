@@ -72,6 +72,8 @@ void qgemm(Prec p, const QView& A, const QView& B, int64_t M, int64_t N, int64_t
 
 // Number of workgroups a configuration launches for an M x N output (sizes scratch).
 int64_t qgemm_blocks(Prec p, int cfg, int64_t M, int64_t N);
+// Name of a configuration, the narrow form included ("" if there is none).
+const char* config_name(Prec p, int cfg);
 // whether a configuration may be kept for every product of a shape: its partial sums fit the scratch, and K is within the
 // limit of a form that does not flush its sums
 bool config_takes(Prec p, int cfg, int64_t M, int64_t N, int64_t K);

@@ -141,9 +141,8 @@ int Ctx::config_for(Prec p, int64_t M, int64_t N, int64_t K, int64_t lda, int64_
   auto key = std::make_tuple((int)p, M, N, K);
   auto it = tuned.find(key);
   if (it != tuned.end()) return it->second;
-  const int def = default_config(p, M, N, K, lda, ldb);
-  if (def != kNarrowConfig && opt.autotune && !no_alloc) return autotune(*this, p, M, N, K, nullptr, s);
-  return def;
+  if (opt.autotune && !no_alloc) return autotune(*this, p, M, N, K, nullptr, s);
+  return default_config(p, M, N, K, lda, ldb);
 }
 
 Mat from_abi(const qpinv_qmat& q) {
@@ -1556,10 +1555,10 @@ int autotune(Ctx& c, Prec p, int64_t M, int64_t N, int64_t K, double* best_ms, h
   hipEvent_t e0, e1;
   QP_HIP(hipEventCreate(&e0));
   QP_HIP(hipEventCreate(&e1));
-  const bool narrow = default_config(p, M, N, K, A.v.ld, B.v.ld) == kNarrowConfig;  // stays the choice where it applies: no tile is faster
   int best = 0;
   double best_t = 1e300;
   std::vector<int> cfgs;
+  if (config_takes(p, kNarrowConfig, M, N, K)) cfgs.push_back(kNarrowConfig);
   for (int cfg = 0; cfg < ncfg; ++cfg)
     if (config_takes(p, cfg, M, N, K)) cfgs.push_back(cfg);
   if (cfgs.empty())
@@ -1567,7 +1566,7 @@ int autotune(Ctx& c, Prec p, int64_t M, int64_t N, int64_t K, double* best_ms, h
   // two timed rounds over all configurations (the first also warms clocks and caches); a
   // configuration's time is its faster round
   const int reps = 3;
-  std::vector<double> tbest(ncfg, 1e300);
+  std::map<int, double> tbest;
   for (int round = 0; round < 2; ++round)
     for (int cfg : cfgs) {
       qgemm(p, A.v, B.v, M, N, K, epi1(C), nullptr, c.scratch, s, cfg);  // warm-up
@@ -1577,11 +1576,13 @@ int autotune(Ctx& c, Prec p, int64_t M, int64_t N, int64_t K, double* best_ms, h
       QP_HIP(hipEventSynchronize(e1));
       float ms = 0.f;
       QP_HIP(hipEventElapsedTime(&ms, e0, e1));
-      tbest[cfg] = std::min(tbest[cfg], (double)ms / reps);
+      const double t = (double)ms / reps;
+      const auto it = tbest.emplace(cfg, t).first;
+      it->second = std::min(it->second, t);
     }
   for (int cfg : cfgs) {
     const double t = tbest[cfg];
-    if (c.opt.verbose) fprintf(stderr, "[qpinv] tune %s %ldx%ldx%ld: %.4f ms\n", tile_configs(p)[cfg].name, (long)M, (long)N, (long)K, t);
+    if (c.opt.verbose) fprintf(stderr, "[qpinv] tune %s %ldx%ldx%ld: %.4f ms\n", config_name(p, cfg), (long)M, (long)N, (long)K, t);
     if (t < best_t) {
       best_t = t;
       best = cfg;
@@ -1589,7 +1590,7 @@ int autotune(Ctx& c, Prec p, int64_t M, int64_t N, int64_t K, double* best_ms, h
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
-  if (!narrow) c.tuned[std::make_tuple((int)p, M, N, K)] = best;
+  c.tuned[std::make_tuple((int)p, M, N, K)] = best;
   if (best_ms) *best_ms = best_t;
   return best;
 }

@@ -43,3 +43,39 @@ def test_tune_file_beyond_a_form_is_skipped(tmp_path):
         kept = _entries((tmp_path / "c.txt").read_text())
     assert ("1", "20", "20", "2048", "f32x8_16x16_regs4") in kept and ("0", "20", "20", "5000", "f64x8_16x16_regs4") in kept
     assert len(kept) == 3
+
+
+def _krylov_names(q, c, n, m):
+    """Configurations of the n x m x n products of a Krylov run."""
+    A = 3.0 * np.eye(n)[None] * np.array([1.0, 0, 0, 0]).reshape(4, 1, 1) + np.random.default_rng(1).standard_normal((4, n, n)) / n
+    B = np.random.default_rng(2).standard_normal((4, n, m))
+    c.set("gemm_timing", 1)
+    q.qpinv_gemm_stats(c.handle)
+    q.gl_krylov(c, to_dev(A, "f64"), to_dev(B, "f64"), tol=0.0, max_iter=3)
+    _, rows = q.qpinv_gemm_stats(c.handle)
+    c.set("gemm_timing", 0)
+    return {q.qpinv_tile_config_name(r["prec"], r["cfg"]) for r in rows}
+
+
+def test_tuned_choice_of_few_columns_is_used(tmp_path):
+    import paper_2605_01464_amd as q
+
+    with q.Context(0) as c:
+        cfg, ms = q.qpinv_autotune(c.handle, q.GEMM_PREC["f64"], 100, 3, 100)
+        name = q.qpinv_tile_config_name(q.GEMM_PREC["f64"], cfg)
+        assert name and ms > 0.0
+        assert _krylov_names(q, c, 100, 3) == {name}
+        assert c.save_tuning(tmp_path / "a.txt") == 1
+        text = (tmp_path / "a.txt").read_text()
+        assert f"gemm 0 100 3 100 {name}" in text.splitlines()
+        A, B = np.random.default_rng(3).standard_normal((2, 4, 100, 100))
+        Ad, Bd = to_dev(A, "f64"), to_dev(B[:, :, :3], "f64")
+        C = q.qgemm(c, Ad, Bd, cfg=cfg)
+        assert rel_fro(to_np(C), Q.qmul(A, B[:, :, :3])) <= 1e-14
+        head = text.splitlines()[0]
+        for line, applied, used in (("gemm 0 100 3 100 f64_64x64x8_w4x4_mfma16", 1, "f64_64x64x8_w4x4_mfma16"),
+                                    ("gemm 0 100 3 100 f64_16x16_narrow", 1, "f64_16x16_narrow"),
+                                    ("gemm 0 100 17 100 f64_16x16_narrow", 0, "f64_16x16_narrow")):
+            (tmp_path / "b.txt").write_text(head + "\n" + line + "\n")
+            assert c.load_tuning(tmp_path / "b.txt") == applied
+            assert _krylov_names(q, c, 100, 3) == {used}
