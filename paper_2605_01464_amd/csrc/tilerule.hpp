@@ -103,16 +103,23 @@ inline int eight_default(Prec p, int64_t M, int64_t N, int64_t K) {
 // (4096^3: 30.8 vs 31.3 ms; 128 x 64 with the same waves 36.6 ms).  BF16 from 1024 tiles
 // of 64 x 64: the staged form with its operand tiles loaded straight into LDS; split BF16: 128 x 128 tiles
 // from 256 of them (one workgroup of 16 waves per CU), 64 x 64 below.  FP32 and FP64 products of other sizes than whole
-// tiles load element by element, and there the 32 x 32 tiles win at every size: they keep two workgroups per unit and
-// waste less at the edges (FP32 2049 x 2047 x 2045: 2.23 ms against 2.67, 4097^3: 16.8 against 17.4; FP64 4.45 against
-// 6.06, and 33.6 against 35.2).  That holds as long as they load element by element, and while their partial sums fit the
-// scratch; beyond (rows x stride from 2^28 on, more than 2^19 tiles) the large tiles stay.
+// tiles load element by element, and there the FP32 32 x 32 tiles win at every size: they keep two workgroups per unit and
+// waste less at the edges (2049 x 2047 x 2045: 2.20 ms against 2.62, 4096 x 4096 x 4104: 16.24 against 16.35, 4097^3: 16.9
+// against 17.3).  In FP64 the rounds decide, of 512 resident 32 x 32 tiles at 0.245 us per k or 256 of 64 x 128 at 0.93:
+// 2049 x 2047 x 2045 4.39 ms against 5.82, 4096 x 4160 x 4096 32.7 against 34.8, but 4096 x 4096 x 4104 32.9 against 30.6,
+// 4096 x 4032 x 4096 31.7 against 30.9, 4096 x 2000 x 2048 8.22 against 7.74.  All that holds as long as they load element by
+// element, and while their partial sums fit the scratch; beyond (rows x stride from 2^28 on, more than 2^19 tiles) the
+// large tiles stay.
 inline int default_config(Prec p, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb) {
   if (p == P_F64E || p == P_F32E) return eight_default(p, M, N, K);
   const int64_t b64 = ((M + 63) / 64) * ((N + 63) / 64);
   const bool whole = M % 64 == 0 && N % (p == P_F64 ? 128 : 64) == 0 && K % 16 == 0;
   const bool small = ((M + 31) / 32) * ((N + 31) / 32) <= kMaxPartials && element_offsets(M, lda, 16, ldb);
-  if (p == P_F64) return N <= 16 ? kNarrowConfig : b64 >= 1024 && (whole || !small) ? 6 : 1;
+  if (p == P_F64) {
+    if (N <= 16) return kNarrowConfig;
+    const int64_t r32 = (((M + 31) / 32) * ((N + 31) / 32) + 511) / 512, r128 = (((M + 63) / 64) * ((N + 127) / 128) + 255) / 256;
+    return b64 >= 1024 && (whole || !small || 0.93 * (double)r128 <= 0.245 * (double)r32) ? 6 : 1;
+  }
   if (p == P_BF16) return b64 >= 1024 ? 11 : b64 >= 256 ? 0 : 1;
   if (p == P_BF16X3) return ((M + 127) / 128) * ((N + 127) / 128) >= 256 ? 4 : 3;
   if (N <= 16) return kNarrowConfig;

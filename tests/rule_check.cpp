@@ -59,6 +59,13 @@ static void lines() {
   CHECK(default_config(P_F32, 4096, 4096, 4096, 4096, 4096) == 5);
   CHECK(default_config(P_F64, 4096, 4096, 4096, 4096, 4096) == 6);
   CHECK(default_config(P_F32, 1024, 1024, 1024, 1024, 1024) == 6);
+  // FP64 off whole tiles: by rounds
+  CHECK(default_config(P_F64, 4096, 4096, 4104, 4104, 4096) == 6);
+  CHECK(default_config(P_F64, 4096, 4032, 4096, 4096, 4032) == 6);
+  CHECK(default_config(P_F64, 4096, 2000, 2048, 2048, 2000) == 6);
+  CHECK(default_config(P_F64, 4096, 4160, 4096, 4096, 4160) == 1);
+  CHECK(default_config(P_F64, 4100, 4100, 4100, 4100, 4100) == 1);
+  CHECK(default_config(P_F64, 3000, 3000, 3000, 3000, 3000) == 1);
   // the register tiles of FP32 end at kRegsMaxK
   CHECK(eight_takes(P_F32E, 2, 300, 300, kRegsMaxK) && !eight_takes(P_F32E, 2, 300, 300, kRegsMaxK + 1));
   CHECK(eight_takes(P_F64E, 2, 300, 300, kRegsMaxK + 1));
