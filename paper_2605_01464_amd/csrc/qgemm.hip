@@ -52,13 +52,17 @@ __global__ void __launch_bounds__(64 * WM * WN, MINW) qgemm_kernel(GemmParams<ty
 // Products of at most 16 columns (a filter's output, the right-hand sides of a Krylov step).  Under 32 x 32 tiles a product of
 // 238 rows is 8 workgroups whose waves each issue all 16 plane products of their K chain.  Here a workgroup has 16 rows and its
 // wave p forms output plane p alone, the four plane products of each k in the same order, so the results are the 32 x 32
-// configuration's bit for bit from a quarter of its MFMAs.  What bounds it is that chain of dependent MFMAs (about 80 ns each).
-// Fragments come straight from global memory, PF blocks of k ahead.  FP64, 238 x 3 x 238: 45 -> 20 us; 401 x 1 x 401: 77 -> 37 us.
-template <class MM, int FLUSH, int PF>
+// configuration's bit for bit from a quarter of its MFMAs.  What bounds it is that chain of dependent MFMAs, at 95 ns each (238
+// x 3 x 238) to 140 (4096 x 16 x 4096) several times the instruction's own latency: the rest goes to addresses, masks and
+// signs formed for every element.  Fragments come straight from global memory, PF = 3 blocks of k ahead (6: 30 and 49 us where 3
+// has 29 and 46).  238 x 3 x 238: 45 -> 29 us; 401 x 1 x 401: 74 -> 46 us.  FP64 only: in FP32 the 32 x 32 tiles, which load element
+// by element there, are as fast or faster (512 x 16 x 512 46 us against 62, 8192 x 16 x 8192 676 against 1903, 238 x 3 x 238 24.5
+// against 23.2).
+template <class MM, int PF>
 __global__ void __launch_bounds__(256, 1) qgemm_narrow_kernel(GemmParams<typename MM::T> P) {
   using T = typename MM::T;
   constexpr int VA = V16<T>::n, KB = VA * MM::KS;
-  static_assert(MM::BLK == 16 && MM::NR == 4 && FLUSH % KB == 0, "16 x 16 MFMA");
+  static_assert(MM::BLK == 16 && MM::NR == 4, "16 x 16 MFMA");
   __shared__ double red_lds[4][2];
   const int tid = threadIdx.x, lane = tid & 63, p = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int fr = MM::fr(lane), fk = MM::fk(lane), m0 = blockIdx.x * 16;
@@ -81,9 +85,9 @@ __global__ void __launch_bounds__(256, 1) qgemm_narrow_kernel(GemmParams<typenam
   };
   // signs of the plane products a_q b_{p ^ q} of output plane p
   const bool n1 = p == 0 || p == 2, n2 = p == 0 || p == 3, n3 = p == 0 || p == 1;
-  typename MM::Acc acc, tot;
+  typename MM::Acc acc;
 #pragma unroll
-  for (int r = 0; r < MM::NR; ++r) acc[r] = tot[r] = T(0);
+  for (int r = 0; r < MM::NR; ++r) acc[r] = T(0);
   const T s1 = n1 ? T(-1) : T(1), s2 = n2 ? T(-1) : T(1), s3 = n3 ? T(-1) : T(1);
   if (nb > 0) {
 #pragma unroll
@@ -108,15 +112,6 @@ __global__ void __launch_bounds__(256, 1) qgemm_narrow_kernel(GemmParams<typenam
         acc = MM::mma(s3 * x[3], y[3], acc);
       }
       load(b0 + d + PF, a[d], w[d]);
-      if constexpr (FLUSH > 0) {
-        if ((b0 + d + 1) * KB % FLUSH == 0) {
-#pragma unroll
-          for (int r = 0; r < MM::NR; ++r) {
-            tot[r] += acc[r];
-            acc[r] = T(0);
-          }
-        }
-      }
     }
   }
   double s_d = 0.0, s_x = 0.0;
@@ -125,7 +120,7 @@ __global__ void __launch_bounds__(256, 1) qgemm_narrow_kernel(GemmParams<typenam
   for (int r = 0; r < MM::NR; ++r) epilogue_inputs_overlap(P, p, m0 + MM::crow(lane, r), MM::ccol(lane), inv[r]);
 #pragma unroll
   for (int r = 0; r < MM::NR; ++r)
-    epilogue_apply(P, p, m0 + MM::crow(lane, r), MM::ccol(lane), FLUSH > 0 ? tot[r] + acc[r] : acc[r], inv[r], s_d, s_x);
+    epilogue_apply(P, p, m0 + MM::crow(lane, r), MM::ccol(lane), acc[r], inv[r], s_d, s_x);
   store_partials<4>(P.partial, s_d, s_x, red_lds, lane, p, tid);
 }
 
@@ -389,13 +384,13 @@ static int64_t config_blocks(Prec p, int cfg, int64_t M, int64_t N, int64_t K) {
 }
 
 const char* config_name(Prec p, int cfg) {
-  if (cfg == kNarrowConfig && (p == P_F64 || p == P_F32)) return p == P_F64 ? "f64_16x16_narrow" : "f32_16x16_narrow";
+  if (cfg == kNarrowConfig && p == P_F64) return "f64_16x16_narrow";
   const auto& t = tile_configs(p);
   return cfg >= 0 && cfg < (int)t.size() ? t[cfg].name : "";
 }
 
 bool config_takes(Prec p, int cfg, int64_t M, int64_t N, int64_t K) {
-  if (cfg == kNarrowConfig && (N > 16 || (p != P_F64 && p != P_F32))) return false;
+  if (cfg == kNarrowConfig && (N > 16 || p != P_F64)) return false;
   if (p == P_F64E || p == P_F32E) return eight_takes(p, cfg, M, N, K);
   return config_blocks(p, cfg, M, N, K) <= kMaxPartials;
 }
@@ -407,7 +402,7 @@ void qgemm(Prec p, const QView& A, const QView& B, int64_t M, int64_t N, int64_t
   if (epi.reduce && (!red || epi.ref >= epi.nin)) throw Error(-1, "qgemm: bad reduction");
   if (cfg < 0) cfg = default_config(p, M, N, K, A.ld, B.ld);
   const auto& cfgs = tile_configs(p);
-  const bool narrow = cfg == kNarrowConfig && (p == P_F64 || p == P_F32) && N <= 16;
+  const bool narrow = cfg == kNarrowConfig && p == P_F64 && N <= 16;
   if (cfg >= (int)cfgs.size() && !narrow) throw Error(-1, "qgemm: bad tile config");
   const int64_t nb = config_blocks(p, cfg, M, N, K);
   if (epi.reduce && nb > scratch.capacity / 2) throw Error(-1, "qgemm: reduction scratch too small");
@@ -417,12 +412,8 @@ void qgemm(Prec p, const QView& A, const QView& B, int64_t M, int64_t N, int64_t
   if (narrow) {
     launched = M == 0 || N == 0 ? 0 : nb;
     if (launched > 0) {
-      if (p == P_F64)
-        hipLaunchKernelGGL((qgemm_narrow_kernel<MM16D, 0, 3>), dim3((unsigned)nb), dim3(256), 0, stream,
-                           make_params<double>(A, B, M, N, K, epi, partial));
-      else
-        hipLaunchKernelGGL((qgemm_narrow_kernel<MM16F, 128, 1>), dim3((unsigned)nb), dim3(256), 0, stream,
-                           make_params<float>(A, B, M, N, K, epi, partial));
+      hipLaunchKernelGGL((qgemm_narrow_kernel<MM16D, 3>), dim3((unsigned)nb), dim3(256), 0, stream,
+                         make_params<double>(A, B, M, N, K, epi, partial));
       QP_HIP(hipGetLastError());
     }
   } else if (p == P_F64E) {

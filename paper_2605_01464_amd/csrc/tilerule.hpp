@@ -9,8 +9,13 @@ namespace qp {
 // P_F64E, P_F32E: FP64 / FP32 with eight real products per quaternion product (qgemm8_kern.hpp); inside the solvers only
 enum Prec : int { P_F64 = 0, P_F32 = 1, P_BF16 = 2, P_BF16X3 = 3, P_F64E = 4, P_F32E = 5 };
 
-// The form for at most 16 columns (qgemm_narrow_kernel), outside the tables; its number in the product statistics
+// The FP64 form for at most 16 columns (qgemm_narrow_kernel), outside the tables; its number in the product statistics
 constexpr int kNarrowConfig = 63;
+
+// It is taken while its workgroups of 16 rows are one round of the 256 compute units.  In a second round 32 x 32 tiles, one
+// of which a unit still has, are faster (FP64, us: 512 x 16 x 512 75 against 88, 401 x 1 x 401 46 against 73, 4096 x 16 x 4096 567
+// against 704; but 8192 x 16 x 8192 2258 against 1399, 100000 x 16 x 512 1817 against 873).
+constexpr int64_t kNarrowRows = 4096;
 
 constexpr int64_t kMaxSide = int64_t(1) << 20;  // rows and columns of a matrix that the library accepts
 
@@ -116,13 +121,12 @@ inline int default_config(Prec p, int64_t M, int64_t N, int64_t K, int64_t lda, 
   const bool whole = M % 64 == 0 && N % (p == P_F64 ? 128 : 64) == 0 && K % 16 == 0;
   const bool small = ((M + 31) / 32) * ((N + 31) / 32) <= kMaxPartials && element_offsets(M, lda, 16, ldb);
   if (p == P_F64) {
-    if (N <= 16) return kNarrowConfig;
+    if (N <= 16 && M <= kNarrowRows) return kNarrowConfig;
     const int64_t r32 = (((M + 31) / 32) * ((N + 31) / 32) + 511) / 512, r128 = (((M + 63) / 64) * ((N + 127) / 128) + 255) / 256;
     return b64 >= 1024 && (whole || !small || 0.93 * (double)r128 <= 0.245 * (double)r32) ? 6 : 1;
   }
   if (p == P_BF16) return b64 >= 1024 ? 11 : b64 >= 256 ? 0 : 1;
   if (p == P_BF16X3) return ((M + 127) / 128) * ((N + 127) / 128) >= 256 ? 4 : 3;
-  if (N <= 16) return kNarrowConfig;
   return b64 >= 1024 && (whole || !small) ? 5 : 6;
 }
 

@@ -59,6 +59,11 @@ static void lines() {
   CHECK(default_config(P_F32, 4096, 4096, 4096, 4096, 4096) == 5);
   CHECK(default_config(P_F64, 4096, 4096, 4096, 4096, 4096) == 6);
   CHECK(default_config(P_F32, 1024, 1024, 1024, 1024, 1024) == 6);
+  // few columns
+  CHECK(default_config(P_F64, 4096, 16, 4096, 4096, 16) == kNarrowConfig && default_config(P_F64, 1, 1, 1, 1, 1) == kNarrowConfig);
+  CHECK(default_config(P_F64, 4097, 16, 4096, 4096, 16) == 1 && default_config(P_F64, 100000, 16, 512, 512, 16) == 1);
+  CHECK(default_config(P_F32, 238, 3, 238, 238, 3) == 6 && default_config(P_F32, 100000, 16, 512, 512, 16) == 6);
+  CHECK(default_config(P_F64, 4096, 17, 4096, 4096, 17) == 1);
   // FP64 off whole tiles: by rounds
   CHECK(default_config(P_F64, 4096, 4096, 4104, 4104, 4096) == 6);
   CHECK(default_config(P_F64, 4096, 4032, 4096, 4096, 4032) == 6);
