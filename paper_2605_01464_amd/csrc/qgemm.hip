@@ -220,7 +220,9 @@ static KernelLimits kernel_limits(K kern, int threads) {
 // TileConfig::per_cu.  The operand load mode is the fastest one that the shape and the views allow: kLoadElems takes any
 // product that is not of whole, aligned tiles, but for offsets beyond 32 bits and the FP64 tiles that have fewer elements
 // than threads (FP32, 1345 x 777 x 1001: 343 us against 533 with kLoadScalar; 1344 x 776 x 1000: 340 against 393 with
-// kLoadVec, whose chunks are masked one by one; 513 x 511 x 509: 79 against 112; FP64 gains 2-8 %).
+// kLoadVec, whose chunks are masked one by one; 513 x 511 x 509: 79 against 112; 500^3 47 against 65).  FP64 gains less, 1-3 %
+// (1000^3 538 us against 555, 5000 x 500 x 5000 6.39 ms against 6.57), and loses 1-7 % where a unit has one workgroup to wait for
+// its loads (500^3 91.2 us against 89.0, 5000 x 28 x 5000 881 against 819): kLoadVec stays for up to one tile a unit.
 // MINW: waves per SIMD the register allocation must leave room for (launch bound).
 template <class MM, int BM, int BN, int BK, int WM, int WN, int FLUSH, bool DB, int MINW, bool WALK, int LM>
 static void launch_mode(const GemmParams<typename MM::T>& P, int64_t grid, size_t dyn_lds, hipStream_t s) {
@@ -235,7 +237,7 @@ static void launch_any_mode(const GemmParams<typename MM::T>& P, int64_t grid, s
   constexpr bool ELEMS = BM * BK % C::NT == 0 && BK * BN % C::NT == 0;
   if (P.vec && P.M % BM == 0 && P.N % BN == 0 && P.K % BK == 0)
     launch_mode<MM, BM, BN, BK, WM, WN, FLUSH, DB, MINW, WALK, kLoadAligned>(P, grid, dyn_lds, s);
-  else if (ELEMS && element_offsets(P.M, P.lda, BK, P.ldb))
+  else if (ELEMS && element_offsets(P.M, P.lda, BK, P.ldb) && !(sizeof(typename MM::T) == 8 && P.vec && grid <= 256))
     launch_mode<MM, BM, BN, BK, WM, WN, FLUSH, DB, MINW, WALK, ELEMS ? kLoadElems : kLoadScalar>(P, grid, dyn_lds, s);
   else if (P.vec)
     launch_mode<MM, BM, BN, BK, WM, WN, FLUSH, DB, MINW, WALK, kLoadVec>(P, grid, dyn_lds, s);
