@@ -37,6 +37,8 @@ __global__ void __launch_bounds__(256) dots_kernel(const double* __restrict__ V,
 // run: 4 us) is the floor, and with one thread per element fetching its own operands every step waited for memory (118 us on
 // average at L = 2856 and 1088 steps).  Here a workgroup has 16 elements: its 256 threads fetch CH vectors' 128-byte
 // pieces at a time, a chunk ahead, into LDS, and 16 lanes run the chains from there (average 118 -> 10 us).
+// Vectors of more than kChunked elements have enough threads with one element each, in the same order (below).
+constexpr int64_t kChunked = 16384;
 constexpr int AX_E = 16, AX_CH = 128, AX_U = AX_CH * AX_E / 256;
 __global__ void __launch_bounds__(256) multi_axpy_kernel(const double* __restrict__ V, int64_t L,
                                                          const double* __restrict__ h, int nvec, double sign,
@@ -84,6 +86,24 @@ __global__ void __launch_bounds__(256) multi_axpy_kernel(const double* __restric
   if (tid < AX_E && e0 + tid < L) W[e0 + tid] = fma(sign, acc, W[e0 + tid]);
 }
 
+// The same with one element a thread, U vectors' loads in flight.  What bounds it is memory, where a chunk's 128 rows of the kernel
+// above are loaded for 16 elements however few vectors there are (us, chunks against this; L = 16384: 3.2 against 2.7 at 1 vector,
+// 24.8 against 48 at 1000; L = 32768: 4.4 / 2.7 and 47 / 52; L = 262144: 22 / 2.7 and 492 / 331; L = 1048576: 80 / 4.3 and 666 /
+// 440 at 300).  U = 8 hides the latency of fewer elements (L = 65536: 89 us at 1000 vectors, 234 with U = 2), U = 2 keeps more pages
+// open from 2^18 on (L = 1048576: 176 us at 128 vectors, 212 with U = 8).
+constexpr int64_t kLongVector = int64_t(1) << 18;
+template <int U>
+__global__ void __launch_bounds__(256) multi_axpy_long_kernel(const double* __restrict__ V, int64_t L,
+                                                              const double* __restrict__ h, int nvec, double sign,
+                                                              double* __restrict__ W) {
+  for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < L; e += (int64_t)gridDim.x * 256) {
+    double acc = 0.0;
+#pragma unroll U
+    for (int i = 0; i < nvec; ++i) acc = fma(h[i], V[(int64_t)i * L + e], acc);
+    W[e] = fma(sign, acc, W[e]);
+  }
+}
+
 // hn[0] = ||W||_F^2 in dots_kernel's order, Y = W / ||W||_F, and the step's 2 nvec projections and hn to `host` (pinned).
 // Every workgroup forms the norm for itself (the vector is at most kFusedNorm doubles long).
 constexpr int64_t kFusedNorm = 16384;
@@ -123,8 +143,17 @@ __global__ void __launch_bounds__(256) scale_kernel(const double* __restrict__ X
   for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < L; e += (int64_t)gridDim.x * 256) Y[e] = a * X[e];
 }
 
-unsigned axpy_blocks(int64_t L) { return (unsigned)((L + AX_E - 1) / AX_E); }
 unsigned blocks_for(int64_t L) { return (unsigned)std::min<int64_t>((L + 255) / 256, 2048); }
+
+void multi_axpy(const double* V, int64_t L, const double* h, int nvec, double sign, double* W, hipStream_t s) {
+  if (L <= kChunked)
+    hipLaunchKernelGGL(multi_axpy_kernel, dim3((unsigned)((L + AX_E - 1) / AX_E)), dim3(256), 0, s, V, L, h, nvec, sign, W);
+  else if (L < kLongVector)
+    hipLaunchKernelGGL(multi_axpy_long_kernel<8>, dim3(blocks_for(L)), dim3(256), 0, s, V, L, h, nvec, sign, W);
+  else
+    hipLaunchKernelGGL(multi_axpy_long_kernel<2>, dim3(blocks_for(L)), dim3(256), 0, s, V, L, h, nvec, sign, W);
+  QP_HIP(hipGetLastError());
+}
 
 // The context's pinned columns, grown on demand, and events.
 double* krylov_columns(Ctx& c, size_t doubles, int events) {
@@ -237,9 +266,7 @@ KrylovResult gl_krylov(Ctx& c, int method, const Mat& A, const Mat& B, const Mat
     QP_HIP(hipMemcpyAsync(dh, y.data(), sizeof(double) * kk, hipMemcpyHostToDevice, s));
     if (Xdst.v.p != X.v.p)
       QP_HIP(hipMemcpyAsync(Xdst.v.p, X.v.p, sizeof(double) * (size_t)L, hipMemcpyDeviceToDevice, s));
-    hipLaunchKernelGGL(multi_axpy_kernel, dim3(axpy_blocks(L)), dim3(256), 0, s, V, L, dh, kk, 1.0,
-                       static_cast<double*>(Xdst.v.p));
-    QP_HIP(hipGetLastError());
+    multi_axpy(V, L, dh, kk, 1.0, static_cast<double*>(Xdst.v.p), s);
     QP_HIP(hipStreamSynchronize(s));  // y (host) is read by the copy
   };
   // RR = ||B - A Xs||_F / ||B - A X_0||_F
@@ -267,8 +294,7 @@ KrylovResult gl_krylov(Ctx& c, int method, const Mat& A, const Mat& B, const Mat
       double* hp = dh + pass * (j + 1);
       hipLaunchKernelGGL(dots_kernel, dim3(j + 1), dim3(256), 0, s, V, L, w, j + 1, hp);
       QP_HIP(hipGetLastError());
-      hipLaunchKernelGGL(multi_axpy_kernel, dim3(axpy_blocks(L)), dim3(256), 0, s, V, L, hp, j + 1, -1.0, w);
-      QP_HIP(hipGetLastError());
+      multi_axpy(V, L, hp, j + 1, -1.0, w, s);
     }
     double* host = columns + (j % kRing) * ring;
     double* next = V + (int64_t)(j + 1) * L;
