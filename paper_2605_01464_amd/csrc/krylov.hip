@@ -4,6 +4,8 @@
 // device array [k][4][n][m] (each V_j also a quaternion-matrix view for the products), the projections
 // are one dot kernel over all previous V_i and one fused multi-axpy (classical Gram-Schmidt, applied
 // twice), and only the small Hessenberg matrix and its Givens rotations are handled on the host.
+#include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <vector>
 
@@ -275,10 +277,13 @@ KrylovResult gl_krylov(Ctx& c, int method, const Mat& A, const Mat& B, const Mat
     return std::sqrt(dot_self(static_cast<double*>(AV.v.p))) / r0;
   };
   // Step j on the stream: W = A V_j (or M A V_j), classical Gram-Schmidt twice (h = V^T W, W -= V h), V_{j+1} = W / ||W||.
-  // Nothing in it waits for the host, which reads the new Hessenberg column from pinned memory kAhead steps behind: the
-  // rotations and the stopping test of one step run while the next ones do (at the end up to kAhead steps are
-  // dropped; they touch only W, AV and basis slots that X does not use).
+  // Nothing in it waits for the host, which reads the new Hessenberg column from pinned memory up to kAhead steps behind: the
+  // rotations and the stopping test of one step run while the next ones do.  The steps in flight at the end are dropped (they
+  // touch only W, AV and basis slots that X does not use), so there are no more of them than the run is long enough for: their
+  // time stays below kTurnaround, about the host's part of a step, for every step done.  (Five steps at 238 x 3 take 469 us with
+  // none in flight and 436 with three; a preconditioned run that ends after one step at 4096 x 16 takes 5.5 ms, and 12.1 with three.)
   constexpr int kAhead = 3, kRing = kAhead + 1;
+  constexpr double kTurnaround = 7e-6;
   const int64_t ring = 2 * (int64_t)max_iter + 1;
   double* const columns = krylov_columns(c, (size_t)(ring * kRing), kRing);
   auto enqueue = [&](int j) {
@@ -310,8 +315,15 @@ KrylovResult gl_krylov(Ctx& c, int method, const Mat& A, const Mat& B, const Mat
   };
   res.status = QPINV_ENOTCONVERGED;
   int queued = 0;
+  using Clock = std::chrono::steady_clock;
+  const Clock::time_point begin = Clock::now();
   for (int j = 0; j < max_iter; ++j) {
-    while (queued < max_iter && queued <= j + kAhead) enqueue(queued++);
+    int ahead = 0;
+    if (j > 0) {
+      const double step = std::chrono::duration<double>(Clock::now() - begin).count() / j;
+      ahead = (int)std::min<double>(kAhead, j * kTurnaround / step);
+    }
+    while (queued < max_iter && queued <= j + ahead) enqueue(queued++);
     QP_HIP(hipEventSynchronize(c.krylov_events[j % kRing]));
     const double* hh = columns + (j % kRing) * ring;
     std::vector<double> col(j + 2, 0.0);
