@@ -98,6 +98,37 @@ __device__ __forceinline__ double wave_sum64(double x) {
   return x;
 }
 
+// Several values of a workgroup in one exchange (every thread gets them): the planes' sums of squares and the union of the flags,
+// a count (exact in any order) and two maxima.
+struct RowTotals {
+  double plane[4], count, max0, max1;
+  unsigned flags;
+};
+__device__ __forceinline__ void workgroup_totals(RowTotals& t) {
+  __shared__ RowTotals part[4];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    t.flags |= __shfl_xor(t.flags, off, 64);
+    t.max0 = fmax(t.max0, __shfl_xor(t.max0, off, 64));
+    t.max1 = fmax(t.max1, __shfl_xor(t.max1, off, 64));
+  }
+#pragma unroll
+  for (int p = 0; p < 4; ++p) t.plane[p] = wave_sum64(t.plane[p]);
+  t.count = wave_sum64(t.count);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = t;
+  __syncthreads();
+  t = part[0];
+#pragma unroll
+  for (int w = 1; w < 4; ++w) {
+#pragma unroll
+    for (int p = 0; p < 4; ++p) t.plane[p] += part[w].plane[p];
+    t.count += part[w].count;
+    t.max0 = fmax(t.max0, part[w].max0);
+    t.max1 = fmax(t.max1, part[w].max1);
+    t.flags |= part[w].flags;
+  }
+}
+
 __device__ __forceinline__ double block_max256(double v, double* sh) {
   sh[threadIdx.x] = v;
   __syncthreads();
@@ -195,50 +226,35 @@ __global__ void __launch_bounds__(256) norms_row_kernel(const T* __restrict__ A,
                                                         double* __restrict__ row_nf, double* __restrict__ planes) {
   __shared__ double sh[256];
   const int i = blockIdx.x;
-  double sa = 0.0, sq = 0.0, nf = 0.0, pl[4] = {0.0, 0.0, 0.0, 0.0};
-  unsigned nz = 0;
+  double sa = 0.0, sq = 0.0;
+  RowTotals t{};
   for (int j = threadIdx.x; j < n; j += 256) {
     double q2 = 0.0;
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
       const double v = (double)A[p * psa + (int64_t)i * lda + j];
-      if (!isfinite(v)) nf += 1.0;
+      if (!isfinite(v)) t.count += 1.0;
       q2 += v * v;
-      pl[p] += v * v;
-      nz |= v != 0.0 ? 1u << p : 0u;
+      t.plane[p] += v * v;
+      t.flags |= v != 0.0 ? 1u << p : 0u;
     }
     sq += q2;
     sa += sqrt(q2);
   }
   sa = block_sum256(sa, sh);
   sq = block_sum256(sq, sh);
-  nf = block_sum256(nf, sh);
+  workgroup_totals(t);
   if (threadIdx.x == 0) {
     row_abs[i] = sa;
     row_sq[i] = sq;
-    row_nf[i] = nf;
-  }
-  if (planes == nullptr) return;
-  __shared__ double shp[4][4];
-  __shared__ unsigned shz[4];
-  const int w = threadIdx.x >> 6;
-  unsigned bits = 0;
+    row_nf[i] = t.count;
+    if (planes) {
+      const int64_t m = gridDim.x;
 #pragma unroll
-  for (int p = 0; p < 4; ++p) {
-    const double t = wave_sum64(pl[p]);
-    if (__ballot((nz >> p) & 1u) != 0) bits |= 1u << p;
-    if ((threadIdx.x & 63) == 0) shp[w][p] = t;
-  }
-  if ((threadIdx.x & 63) == 0) shz[w] = bits;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double q[4];
-    for (int p = 0; p < 4; ++p) {
-      q[p] = ((shp[0][p] + shp[1][p]) + shp[2][p]) + shp[3][p];
-      planes[(int64_t)p * gridDim.x + i] = q[p];
+      for (int p = 0; p < 4; ++p) planes[p * m + i] = t.plane[p];
+      const bool weak = weak_planes(t.plane[0], t.plane[1], t.plane[2], t.plane[3], t.flags, kRowPairRatio);
+      planes[4 * m + i] = (double)(t.flags | (weak ? 16u : 0u));
     }
-    bits = shz[0] | shz[1] | shz[2] | shz[3];
-    planes[4 * (int64_t)gridDim.x + i] = (double)(bits | (weak_planes(q[0], q[1], q[2], q[3], bits, kRowPairRatio) ? 16u : 0u));
   }
 }
 
@@ -298,45 +314,37 @@ __global__ void __launch_bounds__(256) norms_final_kernel(const double* __restri
                                                           int ncmax, const double* __restrict__ planes,
                                                           double* __restrict__ out) {
   __shared__ double sh[256];
-  double fro = 0.0, rmax = 0.0, nf = 0.0, cmax = 0.0;
+  double fro = 0.0;
+  RowTotals t{};  // max0: of the rows, max1: of the columns
   for (int i = threadIdx.x; i < m; i += 256) {
     fro += row_sq[i];
-    rmax = fmax(rmax, row_abs[i]);
-    nf += row_nf[i];
+    t.max0 = fmax(t.max0, row_abs[i]);
+    t.count += row_nf[i];
+    if (planes) {
+#pragma unroll
+      for (int p = 0; p < 4; ++p) t.plane[p] += planes[(int64_t)p * m + i];
+      t.flags |= (unsigned)planes[4 * (int64_t)m + i];
+    }
   }
   if (ncmax > 0) {
-    for (int j = threadIdx.x; j < ncmax; j += 256) cmax = fmax(cmax, cmax_part[j]);
+    for (int j = threadIdx.x; j < ncmax; j += 256) t.max1 = fmax(t.max1, cmax_part[j]);
   } else {
     for (int j = threadIdx.x; j < n; j += 256) {
       double c = 0.0;
       for (int rb = 0; rb < nrb; ++rb) c += col_part[(int64_t)rb * n + j];
-      cmax = fmax(cmax, c);
+      t.max1 = fmax(t.max1, c);
     }
   }
   fro = block_sum256(fro, sh);
-  nf = block_sum256(nf, sh);
-  rmax = block_max256(rmax, sh);
-  cmax = block_max256(cmax, sh);
+  workgroup_totals(t);
   if (threadIdx.x == 0) {
     out[0] = fro;
-    out[1] = cmax;
-    out[2] = rmax;
-    out[3] = nf;
+    out[1] = t.max1;
+    out[2] = t.max0;
+    out[3] = t.count;
+    if (planes)
+      out[4] = (t.flags & 16u) || weak_planes(t.plane[0], t.plane[1], t.plane[2], t.plane[3], t.flags, kPairRatio) ? 1.0 : 0.0;
   }
-  if (planes == nullptr) return;
-  __shared__ unsigned bits;
-  if (threadIdx.x == 0) bits = 0;
-  double q[4] = {0.0, 0.0, 0.0, 0.0};
-  unsigned mine = 0;
-  for (int i = threadIdx.x; i < m; i += 256) {
-#pragma unroll
-    for (int p = 0; p < 4; ++p) q[p] += planes[(int64_t)p * m + i];
-    mine |= (unsigned)planes[4 * (int64_t)m + i];
-  }
-  for (int p = 0; p < 4; ++p) q[p] = block_sum256(q[p], sh);
-  atomicOr(&bits, mine);
-  __syncthreads();
-  if (threadIdx.x == 0) out[4] = (bits & 16u) || weak_planes(q[0], q[1], q[2], q[3], bits, kPairRatio) ? 1.0 : 0.0;
 }
 
 int64_t norms_work_doubles(int64_t m, int64_t n) {

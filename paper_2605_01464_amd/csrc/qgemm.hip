@@ -406,15 +406,14 @@ void qgemm(Prec p, const QView& A, const QView& B, int64_t M, int64_t N, int64_t
   const auto& cfgs = tile_configs(p);
   const bool narrow = cfg == kNarrowConfig && p == P_F64 && N <= 16;
   if (cfg >= (int)cfgs.size() && !narrow) throw Error(-1, "qgemm: bad tile config");
-  const int64_t nb = config_blocks(p, cfg, M, N, K);
-  if (epi.reduce && nb > scratch.capacity / 2) throw Error(-1, "qgemm: reduction scratch too small");
+  if (epi.reduce && config_blocks(p, cfg, M, N, K) > scratch.capacity / 2) throw Error(-1, "qgemm: reduction scratch too small");
   double* partial = epi.reduce ? scratch.partial : nullptr;
   int64_t launched = 0;
   if ((p == P_F64E || p == P_F32E) && !(eight_fits(p, A, B, M, N, K) && eight_takes(p, cfg, M, N, K))) throw Error(-1, "qgemm: operands of the eight-product form");
   if (narrow) {
-    launched = M == 0 || N == 0 ? 0 : nb;
+    launched = M == 0 || N == 0 ? 0 : (M + 15) / 16;
     if (launched > 0) {
-      hipLaunchKernelGGL((qgemm_narrow_kernel<MM16D, 3>), dim3((unsigned)nb), dim3(256), 0, stream,
+      hipLaunchKernelGGL((qgemm_narrow_kernel<MM16D, 3>), dim3((unsigned)launched), dim3(256), 0, stream,
                          make_params<double>(A, B, M, N, K, epi, partial));
       QP_HIP(hipGetLastError());
     }

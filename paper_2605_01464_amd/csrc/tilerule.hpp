@@ -85,7 +85,9 @@ inline int64_t eight_blocks(Prec p, int cfg, int64_t M, int64_t N, int64_t K) {
 
 // whether a configuration may be used for a shape: K within its limit, its partial sums within the scratch
 inline bool eight_takes(Prec p, int cfg, int64_t M, int64_t N, int64_t K) {
-  return takes(p, cfg, K) && eight_blocks(p, cfg, M, N, K) <= kMaxPartials;
+  return takes(p, cfg, K) &&
+         (((M + 15) / 16) * ((N + 15) / 16) <= kMaxPartials ||  // the smallest tiles, more than any launches together have
+          eight_blocks(p, cfg, M, N, K) <= kMaxPartials);
 }
 
 inline int eight_default(Prec p, int64_t M, int64_t N, int64_t K) {
