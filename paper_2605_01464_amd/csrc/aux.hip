@@ -348,20 +348,19 @@ __global__ void __launch_bounds__(256) norms_final_kernel(const double* __restri
 }
 
 int64_t norms_work_doubles(int64_t m, int64_t n) {
-  return 8 * m + (int64_t)col_row_blocks(m) * n + std::max<int64_t>(8, (n + 255) / 256);
+  return 3 * m + (int64_t)col_row_blocks(m) * n + std::max<int64_t>(8, (n + 255) / 256);
 }
 
 template <class T>
-void norms(const QView& A, int64_t m, int64_t n, double* out, double* work, hipStream_t s, bool with_planes) {
+void norms(const QView& A, int64_t m, int64_t n, double* out, double* work, hipStream_t s, double* planes) {
   if (m == 0 || n == 0) {
-    zero_doubles(out, with_planes ? 5 : 4, s);
+    zero_doubles(out, planes ? 5 : 4, s);
     return;
   }
   double* row_abs = work;
   double* row_sq = work + m;
   double* row_nf = work + 2 * m;
-  double* const planes = with_planes ? work + 3 * m : nullptr;
-  double* col_part = work + 8 * m;
+  double* col_part = work + 3 * m;
   const int nrb = col_row_blocks(m);
   hipLaunchKernelGGL((norms_row_kernel<T>), dim3((unsigned)m), dim3(256), 0, s, static_cast<const T*>(A.p), A.ld, A.ps,
                      (int)n, row_abs, row_sq, row_nf, planes);
@@ -382,8 +381,8 @@ void norms(const QView& A, int64_t m, int64_t n, double* out, double* work, hipS
   QP_HIP(hipGetLastError());
 }
 
-template void norms<float>(const QView&, int64_t, int64_t, double*, double*, hipStream_t, bool);
-template void norms<double>(const QView&, int64_t, int64_t, double*, double*, hipStream_t, bool);
+template void norms<float>(const QView&, int64_t, int64_t, double*, double*, hipStream_t, double*);
+template void norms<double>(const QView&, int64_t, int64_t, double*, double*, hipStream_t, double*);
 
 // ------------------------------------------------------------------------------------------------
 // power iteration on A^H A

@@ -757,10 +757,15 @@ void x0_into(const Mat& A, double alpha, const Mat& X, hipStream_t s) {
 // norms of a matrix into host h[0..4] = {||M||_F^2, ||M||_1, ||M||_inf, nonfinite count, weak planes (planes.hpp)}
 void norms_host(Ctx& c, const Mat& M, double h[5], hipStream_t s) {
   double* work = static_cast<double*>(c.ws.get("normwork", sizeof(double) * norms_work_doubles(M.rows, M.cols)));
+  // the rows' plane sums go to the products' scratch, which an allocation-free call's workspace bound need not hold; it has
+  // room for more rows than such a call takes
+  double* planes = 5 * M.rows <= c.scratch.capacity
+                       ? c.scratch.partial
+                       : static_cast<double*>(c.ws.get("normplanes", sizeof(double) * 5 * (size_t)M.rows));
   if (M.dtype == QPINV_F32)
-    norms<float>(M.v, M.rows, M.cols, c.dsc + 8, work, s, true);
+    norms<float>(M.v, M.rows, M.cols, c.dsc + 8, work, s, planes);
   else
-    norms<double>(M.v, M.rows, M.cols, c.dsc + 8, work, s, true);
+    norms<double>(M.v, M.rows, M.cols, c.dsc + 8, work, s, planes);
   to_host(c, c.dsc + 8, 5, s);
   std::memcpy(h, c.hsc, sizeof(double) * 5);
 }

@@ -125,3 +125,35 @@ def test_rule(qctx, dtype):
     B = np.zeros_like(A)  # a plane whose squares underflow is not a zero plane
     B[0], B[2] = A[0], A[2] * (1e-170 if dtype == "f64" else 1e-30)
     assert _forms(q, qctx, B, dtype) == {False}
+
+
+@pytest.mark.parametrize("dtype,m,n", [("f64", 21, 671), ("f64", 116, 473), ("f64", 173, 370), ("f32", 5, 760), ("f32", 64, 661)])
+def test_largest_allocation_free_shapes(qctx, dtype, m, n):
+    """Shapes whose workspace bound just fits the allocation-free scratch: looking at the planes takes none of it."""
+    import torch
+
+    import paper_2605_01464_amd as q
+
+    qctx.set("autotune", 0)
+    A = to_dev(np.random.default_rng(m).standard_normal((4, m, n)), dtype)
+    X = torch.empty((4, n, m), dtype=A.dtype, device="cuda")
+    info = q.solve_noalloc(qctx, A, X, "qhpi19", precision=dtype, check=False)
+    assert info["status"] == q.OK
+    assert torch.equal(X, q.solve(qctx, A, "qhpi19", precision=dtype)[0])
+
+
+@pytest.mark.parametrize("m,n", [(209716, 16), (16, 209716)])
+def test_rows_beyond_the_scratch(qctx, m, n):
+    """More rows than the products' scratch holds sums for."""
+    import torch
+
+    import paper_2605_01464_amd as q
+
+    A = torch.randn(4, m, n, dtype=torch.float64, device="cuda", generator=torch.Generator("cuda").manual_seed(4))
+    X, info = q.solve(qctx, A, "qhpi19", tol=1e-9)
+    assert info["status"] == q.OK
+    P = [[X[i] @ A[j] if m > n else A[i] @ X[j] for j in range(4)] for i in range(4)]
+    I = torch.stack([P[0][0] - P[1][1] - P[2][2] - P[3][3], P[0][1] + P[1][0] + P[2][3] - P[3][2],
+                     P[0][2] - P[1][3] + P[2][0] + P[3][1], P[0][3] + P[1][2] - P[2][1] + P[3][0]])
+    I[0] -= torch.eye(16, dtype=torch.float64, device="cuda")
+    assert I.abs().max().item() <= 1e-11
