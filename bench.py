@@ -77,7 +77,7 @@ def qgemm_rate(q, ctx, M, N, K, prec="f32", reps=20, check_rows=16):
             "frac_peak": 32.0 * M * N * K / (ms * 1e-3) / 1e12 / PEAK[prec], "rel_err_sampled_rows": err}
 
 
-KERNEL_SOURCES = ("common.hpp", "qgemm.hpp", "qgemm_kern.hpp", "qgemm.hip", "qgemm8_kern.hpp", "qgemm8.hip")
+KERNEL_SOURCES = ("common.hpp", "qgemm.hpp", "qgemm_kern.hpp", "qgemm.hip", "qgemm8_kern.hpp", "qgemm8.hip", "tilerule.hpp")
 
 
 def measured_traffic(config_name):

@@ -215,8 +215,7 @@ template void fill_pattern<double>(double*, int64_t, hipStream_t);
 
 // ------------------------------------------------------------------------------------------------
 // norms: row pass (one workgroup per row), column pass (column strips x row blocks), finalize.  With `planes` the row pass also
-// leaves the sums of squares of the row's planes (planes[p m + i]) and, at planes[4 m + i], the bits of its planes that are not
-// zero, plus 16 if its planes are weak (planes.hpp).
+// leaves the sums of squares of the row's planes (planes[p m + i]) and, at planes[4 m + i], its flags (planes.hpp).
 // ------------------------------------------------------------------------------------------------
 static int col_row_blocks(int64_t m) { return (int)std::max<int64_t>(1, std::min<int64_t>(64, (m + 63) / 64)); }
 
@@ -252,8 +251,7 @@ __global__ void __launch_bounds__(256) norms_row_kernel(const T* __restrict__ A,
       const int64_t m = gridDim.x;
 #pragma unroll
       for (int p = 0; p < 4; ++p) planes[p * m + i] = t.plane[p];
-      const bool weak = weak_planes(t.plane[0], t.plane[1], t.plane[2], t.plane[3], t.flags, kRowPairRatio);
-      planes[4 * m + i] = (double)(t.flags | (weak ? 16u : 0u));
+      planes[4 * m + i] = (double)(t.flags | plane_flags(t.plane[0], t.plane[1], t.plane[2], t.plane[3], t.flags, kRowPairRatio));
     }
   }
 }
@@ -343,7 +341,7 @@ __global__ void __launch_bounds__(256) norms_final_kernel(const double* __restri
     out[2] = t.max0;
     out[3] = t.count;
     if (planes)
-      out[4] = (t.flags & 16u) || weak_planes(t.plane[0], t.plane[1], t.plane[2], t.plane[3], t.flags, kPairRatio) ? 1.0 : 0.0;
+      out[4] = (double)(t.flags | plane_flags(t.plane[0], t.plane[1], t.plane[2], t.plane[3], t.flags & 15u, kPairRatio));
   }
 }
 

@@ -17,7 +17,7 @@ void convert(const QView& X, const QView& Y, int64_t rows, int64_t cols, hipStre
 // Scaling features of A (m x n) written to out[0..3] (device doubles):
 //   out[0] = ||A||_F^2, out[1] = ||A||_1 (max column sum of moduli), out[2] = ||A||_inf (max row sum),
 //   out[3] = number of non-finite components,
-// and with `planes` (5 m doubles of work) to out[4]: 1 if its planes are weak in the sense of planes.hpp, else 0.
+// and with `planes` (5 m doubles of work) to out[4] its flags and its rows' (planes.hpp).
 // `work` must hold norms_work_doubles(m, n) doubles.
 template <class T>
 void norms(const QView& A, int64_t m, int64_t n, double* out, double* work, hipStream_t s, double* planes = nullptr);

@@ -432,7 +432,7 @@ __device__ __forceinline__ bool setup_matrix(int scaling, int power_steps, unsig
   // one wave per row, lanes along the row: coalesced, 4 chunks of 64 columns in flight per wave
   constexpr int NG = 4;
   double fro2 = 0.0, nf = 0.0, tot[4] = {0.0, 0.0, 0.0, 0.0};  // (tot: the planes' sums over this wave's rows)
-  unsigned seen = 0;  // its planes that are not zero, and 16 once a row's planes are weak
+  unsigned seen = 0;  // its planes that are not zero, and kPlanesWeak once a row's planes are weak
   for (int i = tid >> 6; i < m; i += nw) {
     double pl[4] = {0.0, 0.0, 0.0, 0.0};
     unsigned nz = 0;
@@ -480,7 +480,7 @@ __device__ __forceinline__ bool setup_matrix(int scaling, int power_steps, unsig
         tot[p] += pl[p];
         if (__ballot((nz >> p) & 1u) != 0) bits |= 1u << p;
       }
-      seen |= bits | (weak_planes(pl[0], pl[1], pl[2], pl[3], bits, kRowPairRatio) ? 16u : 0u);
+      seen |= bits | (plane_flags(pl[0], pl[1], pl[2], pl[3], bits, kRowPairRatio) & kPlanesWeak);
     }
   }
   fro2 = wg_sum(fro2, sh);
@@ -496,7 +496,7 @@ __device__ __forceinline__ bool setup_matrix(int scaling, int power_steps, unsig
     seen = 0;
 #pragma unroll
     for (int p = 0; p < 5; ++p, d /= 32) seen |= d % 32 != 0 ? 1u << p : 0u;
-    weak = (seen & 16u) != 0 || weak_planes(tot[0], tot[1], tot[2], tot[3], seen, kPairRatio);
+    weak = ((seen | plane_flags(tot[0], tot[1], tot[2], tot[3], seen & 15u, kPairRatio)) & kPlanesWeak) != 0;
   } else {
     weak = false;
   }

@@ -68,7 +68,8 @@ struct Entry8 {
 };
 
 // Three tiles each: 64 x 64 (8 waves, one workgroup per compute unit) and 32 x 32 (4 waves, two per unit) through LDS, and
-// 16 x 16 in registers (4 waves, each every fourth block of k; three workgroups per unit in FP64, four in FP32).
+// 16 x 16 in registers (4 waves, each every fourth block of k; 131 and 92 registers, three workgroups per unit in FP64 and five
+// in FP32).
 static const std::vector<Entry8<double>>& f64_table8() {
   static const std::vector<Entry8<double>> t = {
       {{0, 64, 64, 8, 512, "f64x8_64x64_w2x4"}, launch8<MM16D, 64, 64, 2, 4, 2, 0, 2>},

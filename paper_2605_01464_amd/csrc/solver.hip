@@ -14,6 +14,7 @@
 #include "batched.hpp"
 #include "controller.hpp"
 #include "mlp.hpp"
+#include "planes.hpp"
 #include "solver.hpp"
 
 namespace qp {
@@ -754,7 +755,7 @@ void x0_into(const Mat& A, double alpha, const Mat& X, hipStream_t s) {
     x0_scaled_adjoint<double, double>(A.v, A.rows, A.cols, alpha, X.v, s);
 }
 
-// norms of a matrix into host h[0..4] = {||M||_F^2, ||M||_1, ||M||_inf, nonfinite count, weak planes (planes.hpp)}
+// norms of a matrix into host h[0..4] = {||M||_F^2, ||M||_1, ||M||_inf, nonfinite count, flags of its planes (planes.hpp)}
 void norms_host(Ctx& c, const Mat& M, double h[5], hipStream_t s) {
   double* work = static_cast<double*>(c.ws.get("normwork", sizeof(double) * norms_work_doubles(M.rows, M.cols)));
   // the rows' plane sums go to the products' scratch, which an allocation-free call's workspace bound need not hold; it has
@@ -948,7 +949,7 @@ int solve(Ctx& c, int method, int order, const qpinv_qmat* Aq, int scaling, doub
     Ctx& c;
     EightScope(Ctx& cx, bool on) : c(cx) { c.eight = on; }
     ~EightScope() { c.eight = false; }
-  } eight_scope(c, nh[4] == 0.0 && !small_takes(method, order, QPINV_ALPHA_POWER, stop, precision, m, n) &&
+  } eight_scope(c, ((unsigned)nh[4] & (kPlanesWeak | (scaling == QPINV_X0_GIVEN ? kPlanesApart : 0u))) == 0 && !small_takes(method, order, QPINV_ALPHA_POWER, stop, precision, m, n) &&
                        normA > (precision == QPINV_PREC_F64 ? 1e-100 : 1e-12) &&
                        normA < (precision == QPINV_PREC_F64 ? 1e100 : 1e12));
 

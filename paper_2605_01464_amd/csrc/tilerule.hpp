@@ -38,6 +38,7 @@ inline bool element_offsets(int64_t M, int64_t lda, int64_t bk, int64_t ldb) {
 //   K = 1000, 1000 x 1000: 64 x 64 300   32 x 32 346   16 x 16 377    (565)
 //   K = 4096, 4096 x 4096: 64 x 64 16830 32 x 32 19400                (30600; 65.3 TFLOP/s of MFMA work)
 // and FP32: 300^3 48 / 22 / 12 (41), 700^3 107 / 72 / 76 (138), 1000^3 162 / 195 / 234 (320), 4096^3 8720 / 10320 (15920).
+// (The register tiles' caps belong to the fit: they are two and three workgroups a unit, where three and five fit.)
 struct Cost {
   int64_t tile, cap;
   double full, part, fixed;

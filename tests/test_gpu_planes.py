@@ -37,11 +37,14 @@ def _mul(A, B):
     return np.stack([sum(s[p][q] * (A[q] @ B[p ^ q]) for q in range(4)) for p in range(4)])
 
 
-def _check(A, X1, alpha, dtype):
+def _start(A, alpha):
+    return alpha * np.array([1.0, -1.0, -1.0, -1.0]).reshape(4, 1, 1) * A.transpose(0, 2, 1)
+
+
+def _check(A, X1, X0, dtype):
     u = 2.0 ** -53 if dtype == "f64" else 2.0 ** -24
     _, m, n = A.shape
     k1, k2 = max(m, n), min(m, n)
-    X0 = alpha * np.array([1.0, -1.0, -1.0, -1.0]).reshape(4, 1, 1) * A.transpose(0, 2, 1)
     left = m > n
     pair = (lambda T, X: (T, X)) if left else (lambda T, X: (X, T))
     T = -_mul(*((X0, A) if left else (A, X0)))
@@ -70,7 +73,7 @@ def test_weak_planes_keep_their_digits(qctx, dtype, m, n, kind, eps):
     X, info = q.solve(qctx, to_dev(A, dtype), "ns", scaling="given", alpha=alpha, tol=0.0, max_iter=1, stop="guarded",
                       precision=dtype)
     assert info["iters"] == 1
-    _check(A, to_np(X), alpha, dtype)
+    _check(A, to_np(X), _start(A, alpha), dtype)
 
 
 @pytest.mark.parametrize("cfg", [0, 3, 5, 6, 7])
@@ -87,7 +90,7 @@ def test_weak_planes_in_a_batch(qctx, cfg):
         qctx.set("batched_cfg", -1)
     for A, a, X, info in zip(As, alphas, Xs, infos):
         assert info["iters"] == 1
-        _check(A, to_np(X), a, "f32")
+        _check(A, to_np(X), _start(A, a), "f32")
 
 
 def _forms(q, ctx, A, dtype):
@@ -157,3 +160,21 @@ def test_rows_beyond_the_scratch(qctx, m, n):
                      P[0][2] - P[1][3] + P[2][0] + P[3][1], P[0][3] + P[1][2] - P[2][1] + P[3][0]])
     I[0] -= torch.eye(16, dtype=torch.float64, device="cuda")
     assert I.abs().max().item() <= 1e-11
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("keep", [(0,), (2,), (0, 1), (2, 3)])
+def test_given_start_with_other_planes(qctx, dtype, keep):
+    """A matrix that the form itself keeps exact, from a start whose other planes are weak: they keep their digits too."""
+    import paper_2605_01464_amd as q
+
+    dt = np.float32 if dtype == "f32" else np.float64
+    A = _matrix("s", 1.0, 90, 70, dtype)
+    A[[p for p in range(4) if p not in keep]] = 0.0
+    X0 = _start(A, 1.0 / np.sum(A * A)) + 1e-7 * np.random.default_rng(8).standard_normal((4, 70, 90)) * np.array(
+        [float(p not in keep) for p in range(4)]).reshape(4, 1, 1)
+    X0 = X0.astype(dt).astype(np.float64)
+    X, info = q.solve(qctx, to_dev(A, dtype), "ns", scaling="x0", tol=0.0, max_iter=1, stop="guarded", precision=dtype,
+                      X=to_dev(X0, dtype))
+    assert info["iters"] == 1
+    _check(A, to_np(X), X0, dtype)
