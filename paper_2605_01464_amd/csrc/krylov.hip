@@ -279,11 +279,12 @@ KrylovResult gl_krylov(Ctx& c, int method, const Mat& A, const Mat& B, const Mat
   // Step j on the stream: W = A V_j (or M A V_j), classical Gram-Schmidt twice (h = V^T W, W -= V h), V_{j+1} = W / ||W||.
   // Nothing in it waits for the host, which reads the new Hessenberg column from pinned memory up to kAhead steps behind: the
   // rotations and the stopping test of one step run while the next ones do.  The steps in flight at the end are dropped (they
-  // touch only W, AV and basis slots that X does not use), so there are no more of them than the run is long enough for: their
-  // time stays below kTurnaround, about the host's part of a step, for every step done.  (Five steps at 238 x 3 take 469 us with
-  // none in flight and 436 with three; a preconditioned run that ends after one step at 4096 x 16 takes 5.5 ms, and 12.1 with three.)
+  // touch only W, AV and basis slots that X does not use), so they are as many as the run is long enough for: kAheadTime of them
+  // for every step done, a third of a step at 238 x 3 (66 us) and a fortieth of one of a millisecond, whose host part is nothing.
+  // (Five steps at 238 x 3 take 469 us with none in flight and 436 with three from the start; a preconditioned run that ends after
+  // one step at 4096 x 16 takes 5.5 ms, and 12.1 with three from the start.)
   constexpr int kAhead = 3, kRing = kAhead + 1;
-  constexpr double kTurnaround = 7e-6;
+  constexpr double kAheadTime = 25e-6;
   const int64_t ring = 2 * (int64_t)max_iter + 1;
   double* const columns = krylov_columns(c, (size_t)(ring * kRing), kRing);
   auto enqueue = [&](int j) {
@@ -316,12 +317,13 @@ KrylovResult gl_krylov(Ctx& c, int method, const Mat& A, const Mat& B, const Mat
   res.status = QPINV_ENOTCONVERGED;
   int queued = 0;
   using Clock = std::chrono::steady_clock;
-  const Clock::time_point begin = Clock::now();
+  Clock::time_point first;  // when the first step had ended
   for (int j = 0; j < max_iter; ++j) {
     int ahead = 0;
-    if (j > 0) {
-      const double step = std::chrono::duration<double>(Clock::now() - begin).count() / j;
-      ahead = (int)std::min<double>(kAhead, j * kTurnaround / step);
+    if (j == 1) first = Clock::now();
+    if (j > 1) {
+      const double step = std::chrono::duration<double>(Clock::now() - first).count() / (j - 1);
+      ahead = (int)std::min<double>(kAhead, j * kAheadTime / step);
     }
     while (queued < max_iter && queued <= j + ahead) enqueue(queued++);
     QP_HIP(hipEventSynchronize(c.krylov_events[j % kRing]));
