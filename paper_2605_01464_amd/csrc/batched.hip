@@ -878,7 +878,7 @@ __global__ void __launch_bounds__(64 * WM * WN) batched_kernel(BParams P) {
       __syncthreads();
       rsj[rs] = j - 1;
 
-      const double d_abs = sqrt(fmax(sd, 0.0)), xn = sqrt(fmax(sx, 0.0));
+      const double d_abs = norm_of(sd), xn = norm_of(sx);
       info.iters = j;
       info.dx_rel = xn > 0.0 ? d_abs / xn : 0.0;
       xn_last2 = xn_last;
@@ -1692,7 +1692,7 @@ __global__ void __launch_bounds__(64 * WM * WN, PER_CU) batched_sync_kernel(SPar
           sx0 += P.partial[d.poff + 2 * q + 1];
         }
         const double sdv = wg_sum(sd0, sh), sxv = wg_sum(sx0, sh);
-        const double d_abs = sqrt(fmax(sdv, 0.0)), xn = sqrt(fmax(sxv, 0.0));
+        const double d_abs = norm_of(sdv), xn = norm_of(sxv);
         const int j = S.j + 1;  // index of the new iterate X_j = buffer nxt
         if (S.j & 1)  // this update's residual belongs to X_{j-1}
           S.rsj1 = S.j;

@@ -19,6 +19,9 @@ namespace qp {
 enum StopRule : int { STOP_DX_ABS = 0, STOP_DX_REL = 1, STOP_E1_REL = 2, STOP_GUARDED = 3 };
 enum Decision : int { D_CONTINUE = 0, D_TOL = 1, D_RISE = 2, D_DIVERGED = 3, D_NEWMIN = 4 };
 
+// A norm from its sum of squares.  Not a number stays one (a maximum with zero would make it 0 and the iterate converged).
+QP_HD __attribute__((always_inline)) inline double norm_of(double sum_sq) { return sum_sq <= 0.0 ? 0.0 : __builtin_sqrt(sum_sq); }
+
 struct StopController {
   int rule;
   double tol;

@@ -934,7 +934,7 @@ __global__ void __launch_bounds__(SM_THREADS) small_solve_kernel(const SmParams<
       // the update X_{j+1} = X_nxt is formed: its change norms summed over the tiles, then the stop rule
       const int tu = P->kind[ph][0] == 1 ? tiles[0] : 0;
       const double d2 = sm_tile_sum(P->partial, tu, 2), x2 = sm_tile_sum(P->partial + 1, tu, 2);
-      const double d_abs = sqrt(fmax(0.0, d2)), xn = sqrt(fmax(0.0, x2));
+      const double d_abs = norm_of(d2), xn = norm_of(x2);
       ++j;
       dx_rel = xn > 0.0 ? d_abs / xn : 0.0;
       const bool diverged = !__builtin_isfinite(d_abs) || !__builtin_isfinite(xn) || xn * normA > 1e20;

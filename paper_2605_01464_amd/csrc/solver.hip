@@ -1118,8 +1118,8 @@ int solve(Ctx& c, int method, int order, const qpinv_qmat* Aq, int scaling, doub
     if (guard_R) {
       // Theorem 1: alpha is admissible iff every |1 - alpha sigma_i^2| < 1; R_0 = I - X_0 A (or I - A X_0)
       // has exactly these eigenvalues (and 1 on the null space), so ||R_0||_2 > 1 means divergence
-      const double r0 = std::sqrt(std::max(0.0, power_host(c, R, 3, s)));
-      if (r0 > 1.0 + 1e-3) {
+      const double r0 = norm_of(power_host(c, R, 3, s));
+      if (!(r0 <= 1.0 + 1e-3)) {
         restart_classical();
         continue;
       }
@@ -1132,10 +1132,10 @@ int solve(Ctx& c, int method, int order, const qpinv_qmat* Aq, int scaling, doub
       rsave_j[slot] = j;
     }
     double rnorm = -1.0;  // ||R_j||_2 estimate: only the BF16 phase's switch rule uses it
-    if (p == P_BF16) rnorm = std::sqrt(std::max(0.0, power_host(c, R, c.opt.mixed_rnorm_steps, s)));
+    if (p == P_BF16) rnorm = norm_of(power_host(c, R, c.opt.mixed_rnorm_steps, s));
     to_host(c, red, 2, s);
-    const double d_abs = std::sqrt(std::max(0.0, c.hsc[0]));
-    const double xn = std::sqrt(std::max(0.0, c.hsc[1]));
+    const double d_abs = norm_of(c.hsc[0]);
+    const double xn = norm_of(c.hsc[1]);
     ++j;
     xnorm_hist.push_back(xn);
     if (p == P_BF16)
@@ -1237,7 +1237,7 @@ int solve(Ctx& c, int method, int order, const qpinv_qmat* Aq, int scaling, doub
     // ---------------------------------------------------------------- main phase: controller
     double e1r = -1.0;
     if (stop == STOP_E1_REL) {
-      e1r = std::sqrt(std::max(0.0, e1_sq(c, p, Adt, S->b[nxt], s))) / normA;
+      e1r = norm_of(e1_sq(c, p, Adt, S->b[nxt], s)) / normA;
       inf.e1_rel = e1r;
     }
     int dec = ctl.update(j, d_abs, xn, e1r);
